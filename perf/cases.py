@@ -1,0 +1,434 @@
+"""Performance cases of the library: what its users have it do, through its public entry points.
+
+Suspensions follow the repository's seeded recipes: unit spheres at volume fraction 0.2 and gap 0.1
+(as spheres_200), or spheroids (a, a, 1) with random orientations, each inside one of those spheres
+(as ellipsoids_10000 places its ellipsoids), with N proxies and M collocation points per body around
+the usual 400 and 800.  `listed` holds the cases of record, `draw` more of the same ranges.
+
+MIXED calls evaluate pairs in FP32: their results, good to about seven digits, are kept as float32.
+FP64 results stay float64.
+"""
+import math
+
+import numpy as np
+import torch
+
+import mfs_workloads as W
+from paper_2409_04215_amd import mfs
+
+DEV = "cuda"
+TOL = 1e-5  # GMRES tolerance of the benchmark
+
+
+def listed():
+    return [
+        # a few bodies, as in a contact study: launches and latency count
+        dict(name="pair_small", op="pair", kind="stokes", prec="mixed", systems=1, bodies=4, n=300, m=600, aspect=1.0),
+        # flow at the collocation points of one suspension of the size of ellipsoids_100
+        dict(name="pair_stokes", op="pair", kind="stokes", prec="mixed", systems=1, bodies=100, n=400, m=800,
+             aspect=2.0),
+        # potentials of a larger suspension of charged bodies, odd sizes
+        dict(name="pair_laplace", op="pair", kind="laplace", prec="mixed", systems=1, bodies=250, n=389, m=777,
+             aspect=2.0),
+        # the same sums in FP64, for residual checks and references; odd sizes
+        dict(name="pair_stokes_fp64", op="pair", kind="stokes", prec="fp64", systems=1, bodies=70, n=331, m=667,
+             aspect=1.0),
+        # gradients of a loss on the flow with respect to strengths and both point sets (shape and position fitting)
+        dict(name="pair_backward", op="pair_backward", kind="stokes", prec="mixed", systems=1, bodies=60, n=400, m=800,
+             aspect=2.0),
+        # surface traction after a solve
+        dict(name="traction", op="traction", kind="stokes", prec="mixed", systems=1, bodies=80, n=400, m=600,
+             aspect=1.0),
+        # one application of the preconditioned operator on a few bodies: the one-body blocks dominate
+        dict(name="matvec_small", op="matvec", kind="stokes", prec="mixed", systems=1, bodies=6, n=400, m=800,
+             aspect=1.0),
+        # the operator over a batch of independent suspensions, half Stokes and half Laplace, a shape for each
+        dict(name="matvec_batch", op="matvec", kind="both", prec="mixed", systems=12, bodies=40, n=200, m=400,
+             aspect=2.0),
+        # the operator on one large suspension: the inner step of the long solves
+        dict(name="matvec_large", op="matvec", kind="stokes", prec="mixed", systems=1, bodies=400, n=400, m=800,
+             aspect=1.0),
+        # the whole mobility solve: right-hand side, GMRES with the FP64 residual check, recovery
+        dict(name="solve", op="solve", kind="stokes", prec="mixed", systems=1, bodies=80, n=300, m=600, aspect=1.0),
+        # gradient of a loss on the velocities with respect to centres and loads: adjoint GMRES and pair gradients
+        dict(name="gradient", op="gradient", kind="stokes", prec="mixed", systems=1, bodies=50, n=300, m=600,
+             aspect=1.0),
+        # plan set-up for a new shape with the library's QR, and the first use of its factors
+        dict(name="setup_qr", op="setup", kind="stokes", prec="fp64", systems=1, bodies=10, n=400, m=800, aspect=2.0),
+    ]
+
+
+# per operation: how often it is drawn, kinds, precisions, largest body count and most work (pairs)
+_RANGES = {
+    "pair": (4, ("stokes", "laplace"), ("mixed", "mixed", "fp64"), 300, 2.5e10),
+    "pair_backward": (1, ("stokes", "laplace"), ("mixed", "fp64"), 80, 2.0e9),
+    "traction": (1, ("stokes",), ("mixed", "fp64"), 100, 3.0e9),
+    "matvec": (3, ("stokes", "laplace", "both"), ("mixed", "mixed", "fp64"), 400, 2.0e10),
+    "solve": (1, ("stokes", "laplace"), ("mixed",), 80, 1.0e9),
+    "gradient": (1, ("stokes",), ("mixed",), 50, 4.0e8),
+    "setup": (1, ("stokes", "laplace"), ("fp64",), 20, 1e10),
+}
+
+
+def draw(rng):
+    ops = [op for op, r in _RANGES.items() for _ in range(r[0])]
+    op = rng.choice(ops)
+    _, kinds, precs, most, pairs = _RANGES[op]
+    c = dict(op=op, kind=rng.choice(kinds), prec=rng.choice(precs), systems=1)
+    c["n"] = int(round(math.exp(rng.uniform(math.log(100), math.log(450)))))
+    c["m"] = int(round(c["n"] * rng.uniform(1.6, 2.4)))
+    c["aspect"] = round(rng.choice((1.0, rng.uniform(1.0, 3.0))), 3)
+    c["bodies"] = int(round(math.exp(rng.uniform(math.log(2 if op == "pair" else 4), math.log(most)))))
+    if op in ("pair", "matvec") and (c["kind"] == "both" or rng.random() < 0.3):
+        c["systems"] = rng.randint(2, 12)
+        c["bodies"] = min(c["bodies"], 60)
+    if c["kind"] == "both":
+        c["n"] = min(c["n"], 200)
+        c["m"] = min(c["m"], 480)
+    cost = 3.0 if c["prec"] == "fp64" else 1.0
+    while c["bodies"] > 2 and cost * _pairs(c) > pairs:
+        c["bodies"] -= 1
+    return c
+
+
+def _bodies_of(c):
+    """Bodies per system: a batch holds suspensions of different sizes."""
+    return [max(1, c["bodies"] * (3 + 4 * (s % 3)) // 7) for s in range(c["systems"])] if c["systems"] > 1 \
+        else [c["bodies"]]
+
+
+def _kinds_of(c):
+    if c["kind"] == "both":
+        return [W.STOKES if s < c["systems"] / 2 else W.LAPLACE for s in range(c["systems"])]
+    return [W.STOKES if c["kind"] == "stokes" else W.LAPLACE] * c["systems"]
+
+
+def _pairs(c):
+    return sum(float(p * c["n"]) * (p * c["m"]) for p in _bodies_of(c))
+
+
+def _workload(c, seed):
+    """The suspension(s) of a case: one shape per system, all made from the seed."""
+    rg = np.random.default_rng([seed, 17])
+    shapes, cens, rots, sob, ptr, nets = [], [], [], [], [0], []
+    unit = np.ones(3)
+    for s, (p, kind) in enumerate(zip(_bodies_of(c), _kinds_of(c))):
+        aspect = c["aspect"] + 0.05 * s
+        shapes.append(W.spheroid_shape(1.0 / aspect, 1.0, c["n"], c["m"]))
+        cen, _ = W.random_cluster(rg, p, unit, W.cube_side(p, unit), 0.1)
+        cens.append(cen)
+        rots.append(np.stack([W.random_rotation(rg) for _ in range(p)]))
+        sob.append(np.full(p, s, np.int32))
+        ptr.append(ptr[-1] + p)
+        nets.append(rg.standard_normal((p, 6)) if kind == W.STOKES else rg.standard_normal(p))
+    return W.Workload("case", shapes, np.concatenate(cens), np.concatenate(rots), np.concatenate(sob),
+                      np.array(ptr, np.int64), np.array(_kinds_of(c), np.int32), nets)
+
+
+def _dev(a):
+    return torch.tensor(np.ascontiguousarray(a), dtype=torch.float64, device=DEV)
+
+
+def _smooth(wl, seed):
+    """A smooth field at the collocation points (a random quadratic per body), the data GMRES works on."""
+    rg = np.random.default_rng([seed, 23])
+    parts = []
+    for s in range(wl.n_sys):
+        dim = 3 if wl.sys_kind[s] == W.STOKES else 1
+        for b in range(int(wl.sys_body_ptr[s]), int(wl.sys_body_ptr[s + 1])):
+            x = wl.shapes[wl.shape_of_body[b]].trg
+            f = np.concatenate([np.ones((len(x), 1)), x, x * x, x * x[:, [1, 2, 0]]], axis=1)
+            parts.append((f @ rg.standard_normal((f.shape[1], dim))).reshape(-1))
+    return np.concatenate(parts)
+
+
+def _points(c, seed):
+    """Structure arrays and point data of the standalone sums."""
+    wl = _workload(c, seed)
+    rg = np.random.default_rng([seed, 29])
+    trg, _ = wl.world_points("trg")
+    src, _ = wl.world_points("src")
+    dim = 3 if c["kind"] == "stokes" else 1
+    shape = lambda k: (k, 3) if dim == 3 else (k,)  # noqa: E731
+    geo = (wl.sys_body_ptr, np.arange(wl.n_body + 1) * c["m"], np.arange(wl.n_body + 1) * c["n"])
+    nrm = np.concatenate([(sh.trg / sh.axes ** 2 / np.linalg.norm(sh.trg / sh.axes ** 2, axis=1, keepdims=True))
+                          @ wl.rot[b].T for b, sh in ((b, wl.shapes[wl.shape_of_body[b]]) for b in range(wl.n_body))])
+    return dict(geo=geo, trg=_dev(trg), src=_dev(src), nrm=_dev(nrm), str=_dev(rg.standard_normal(shape(len(src)))),
+                w=_dev(rg.standard_normal(shape(len(trg)))))
+
+
+def _prec(c):
+    return mfs.MIXED if c["prec"] == "mixed" else mfs.FP64
+
+
+def prepare(case, seed):
+    c = dict(case)
+    st = dict(case=c)
+    if c["op"] in ("pair", "pair_backward", "traction"):
+        st.update(_points(c, seed))
+        return st
+    wl = _workload(c, seed)
+    st["wl"] = wl
+    st["x"] = _dev(_smooth(wl, seed))
+    st["net"] = _dev(np.concatenate([n.reshape(-1) for n in wl.net]))
+    if c["op"] != "setup":
+        st["plan"] = mfs.Plan.from_workload(wl, _prec(c), device=DEV)
+    if c["op"] == "gradient":  # the forward solve is in hand
+        out, info = st["plan"].solve(st["net"], tol=0.1 * TOL)
+        st.update(gamma=info["gamma"], s0=info["s0"], grad=2.0 * out)
+    return st
+
+
+def run(state):
+    c = state["case"]
+    p = _prec(c)
+    keep = (lambda t: t.float()) if c["prec"] == "mixed" else (lambda t: t)  # noqa: E731
+    if c["op"] == "pair":
+        f = mfs.p2p_stokes if c["kind"] == "stokes" else mfs.p2p_laplace
+        return keep(f(*state["geo"], state["trg"], state["src"], state["str"], prec=p))
+    if c["op"] == "pair_backward":
+        f = mfs.p2p_stokes_backward if c["kind"] == "stokes" else mfs.p2p_laplace_backward
+        return [keep(g) for g in f(*state["geo"], state["trg"], state["src"], state["str"], state["w"], prec=p)]
+    if c["op"] == "traction":
+        return keep(mfs.p2p_stokes_traction(*state["geo"], state["trg"], state["nrm"], state["src"], state["str"],
+                                            prec=p))
+    if c["op"] == "matvec":
+        return keep(state["plan"].matvec(state["x"]))
+    if c["op"] == "solve":
+        out, info = state["plan"].solve(state["net"], tol=TOL)
+        return [keep(out), keep(info["gamma"])]
+    if c["op"] == "gradient":
+        gc, gn, _, _, _ = state["plan"].gmres_solve_backward(state["gamma"], state["s0"], state["grad"],
+                                                             tol=0.1 * TOL, want_net=True)
+        return [keep(gc), keep(gn)]
+    plan = mfs.Plan.from_workload(state["wl"], p, device=DEV, factorization=mfs.FACTOR_QR)
+    return keep(plan.precond_apply(state["x"], prec=p))
+
+
+def work(case):
+    """Bytes: points, vectors and factors once.  Flops: 28 a Stokeslet pair, 11 a 1/r pair (FMA 2, rsqrt 1), and
+    the products of the one-body blocks."""
+    c = case
+    byt = flo = 0.0
+    kinds, bodies = _kinds_of(c), _bodies_of(c)
+    for kind, p in zip(kinds, bodies):
+        dim = 3 if kind == W.STOKES else 1
+        n, m = p * c["n"], p * c["m"]
+        pairs = float(n) * m * (1 - 1.0 / p if p > 1 else 1)
+        per = 28 if kind == W.STOKES else 11
+        dn, dm = dim * c["n"], dim * c["m"]
+        e = 4 if c["prec"] == "mixed" else 8
+        if c["op"] == "pair":
+            byt += 8 * (3 * (n + m) + dim * (n + m))
+            flo += per * pairs
+        elif c["op"] == "pair_backward":  # one transposed sum, two gradient sums
+            byt += 8 * (6 * (n + m) + dim * (2 * n + m))
+            flo += (per + 2 * (52 if dim == 3 else 16)) * pairs
+        elif c["op"] == "traction":
+            byt += 8 * (6 * n + 9 * m)
+            flo += 31 * pairs
+        else:
+            factors = dn * (dm + dn)
+            mv_b, mv_f = e * factors + 8 * (2 * dim * m + 3 * n + 3 * m), per * pairs + 2.0 * factors * p
+            if c["op"] == "matvec":
+                byt, flo = byt + mv_b, flo + mv_f
+            elif c["op"] == "solve":  # about 20 iterations and a right-hand side
+                byt, flo = byt + 21 * mv_b, flo + 21 * mv_f
+            elif c["op"] == "gradient":  # about 20 adjoint iterations, two gradient sums, one transposed sum
+                byt, flo = byt + 20 * mv_b, flo + 20 * mv_f + (2 * 52 + per) * pairs
+            else:  # QR, Q and R^-1 of one block, then its application
+                byt += 8 * (3 * (c["n"] + c["m"]) + 2 * factors)
+                flo += 4.0 * dm * dn * dn - 4.0 / 3 * dn ** 3 + dn ** 3 / 3.0 + 2.0 * factors * p
+    return {"bytes": byt, "flops": flo}
+
+
+# ---------------------------------------------------------------------------
+# the same values in plain torch, 64 bits
+# ---------------------------------------------------------------------------
+def _blocks(n_trg, n_src):
+    step = max(1, int(4e7 // max(1, n_src)))
+    return [(a, min(n_trg, a + step)) for a in range(0, n_trg, step)]
+
+
+def _pair_sum(x, y, s, skip=None, stokes=True):
+    """sum_j G(x_i - y_j) s_j over all pairs but those of one body (skip = bodies' points of targets, sources)."""
+    out = torch.zeros(len(x), 3 if stokes else 1, dtype=torch.float64, device=x.device)
+    s = s.reshape(len(y), -1)
+    tb = torch.arange(len(x), device=x.device) // skip[0] if skip else None
+    sb = torch.arange(len(y), device=x.device) // skip[1] if skip else None
+    for a, b in _blocks(len(x), len(y)):
+        d = [x[a:b, None, k] - y[None, :, k] for k in range(3)]
+        ri = torch.rsqrt(d[0] ** 2 + d[1] ** 2 + d[2] ** 2)
+        if skip:
+            ri = ri * (tb[a:b, None] != sb[None, :])
+        if not stokes:
+            out[a:b] = ri @ s / (4 * math.pi)
+            continue
+        df = sum(d[k] * s[None, :, k] for k in range(3)) * ri ** 3
+        out[a:b] = (ri @ s + torch.stack([(df * d[k]).sum(1) for k in range(3)], 1)) / (8 * math.pi)
+    return out
+
+
+def _pair_exact(c, seed):
+    st = _points(c, seed)
+    stokes = c["kind"] == "stokes"
+    outs, sp = [], st["geo"][0]
+    for b0, b1 in zip(sp[:-1], sp[1:]):
+        t, q = slice(b0 * c["m"], b1 * c["m"]), slice(b0 * c["n"], b1 * c["n"])
+        outs.append(_pair_sum(st["trg"][t], st["src"][q], st["str"][q], (c["m"], c["n"]), stokes))
+    out = torch.cat(outs)
+    return out if stokes else out[:, 0]
+
+
+def _traction_exact(c, seed):
+    st = _points(c, seed)
+    x, y, f, nv = st["trg"], st["src"], st["str"], st["nrm"]
+    out = torch.zeros_like(x)
+    for a, b in _blocks(len(x), len(y)):
+        d = [x[a:b, None, k] - y[None, :, k] for k in range(3)]
+        ri = torch.rsqrt(d[0] ** 2 + d[1] ** 2 + d[2] ** 2)
+        t = sum(d[k] * f[None, :, k] for k in range(3)) * sum(d[k] * nv[a:b, None, k] for k in range(3)) * ri ** 5
+        out[a:b] = torch.stack([(t * d[k]).sum(1) for k in range(3)], 1) * (-3 / (4 * math.pi))
+    return out
+
+
+def _backward_exact(c, seed):
+    st = _points(c, seed)
+    x, y, w, s = st["trg"], st["src"], st["w"].reshape(len(st["trg"]), -1), st["str"].reshape(len(st["src"]), -1)
+    stokes = c["kind"] == "stokes"
+    gs = _pair_sum(y, x, w, (c["n"], c["m"]), stokes)
+    gx, gy = torch.zeros_like(x), torch.zeros_like(y)
+    tb, sb = torch.arange(len(x), device=DEV) // c["m"], torch.arange(len(y), device=DEV) // c["n"]
+    for a, b in _blocks(len(x), len(y)):
+        d = [x[a:b, None, k] - y[None, :, k] for k in range(3)]
+        ri = torch.rsqrt(d[0] ** 2 + d[1] ** 2 + d[2] ** 2) * (tb[a:b, None] != sb[None, :])
+        ws = w[a:b] @ s.T
+        if stokes:
+            wd = sum(d[k] * w[a:b, None, k] for k in range(3))
+            sd = sum(d[k] * s[None, :, k] for k in range(3))
+            kk = -ws - 3 * wd * sd * ri ** 2
+            g = [(kk * d[k] + wd * s[None, :, k] + sd * w[a:b, None, k]) * ri ** 3 / (8 * math.pi) for k in range(3)]
+        else:
+            g = [-ws * d[k] * ri ** 3 / (4 * math.pi) for k in range(3)]
+        gx[a:b] = torch.stack([v.sum(1) for v in g], 1)
+        gy -= torch.stack([v.sum(0) for v in g], 1)
+    return [gs if stokes else gs[:, 0], gx, gy]
+
+
+class _Operator:
+    """The square operator of one system, dense one-body blocks and pair sums in 64 bits."""
+
+    def __init__(self, c, wl, s):
+        self.c, self.stokes = c, wl.sys_kind[s] == W.STOKES
+        b0, b1 = int(wl.sys_body_ptr[s]), int(wl.sys_body_ptr[s + 1])
+        sh = wl.shapes[s]
+        self.rot, self.cen = torch.tensor(wl.rot[b0:b1]), torch.tensor(wl.centre[b0:b1])
+        self.xl, self.yl = torch.tensor(sh.trg), torch.tensor(sh.src)
+        world = lambda p: (self.cen[:, None] + p[None] @ self.rot.transpose(1, 2)).reshape(-1, 3).to(DEV)  # noqa: E731
+        self.x, self.y = world(self.xl), world(self.yl)
+        m, n = len(self.xl), len(self.yl)
+        d = self.xl[:, None] - self.yl[None]
+        r = d.norm(dim=2)
+        if self.stokes:
+            S = (torch.eye(3) / r[..., None, None] + d[..., :, None] * d[..., None, :] / r[..., None, None] ** 3)
+            S = (S / (8 * math.pi)).permute(0, 2, 1, 3).reshape(3 * m, 3 * n)
+            self.K = self._rigid(self.yl)
+            self.G = torch.linalg.inv(self.K.T @ self.K)
+            A = S - S @ self.K @ self.G @ self.K.T + self._rigid(self.xl) @ self.K.T
+        else:
+            S = 1 / (4 * math.pi * r)
+            A = S - S.mean(1, keepdim=True) + 1.0 / n
+        q, self.R = torch.linalg.qr(A)
+        self.Qt = q.T.contiguous()
+
+    @staticmethod
+    def _rigid(p):
+        K = torch.zeros(len(p), 3, 6, dtype=torch.float64)
+        K[:, 0, 0] = K[:, 1, 1] = K[:, 2, 2] = 1
+        K[:, 0, 4], K[:, 0, 5], K[:, 1, 3] = p[:, 2], -p[:, 1], -p[:, 2]
+        K[:, 1, 5], K[:, 2, 3], K[:, 2, 4] = p[:, 0], p[:, 1], -p[:, 0]
+        return K.reshape(-1, 6)
+
+    def _turn(self, v, to_world):
+        if not self.stokes:
+            return v
+        R = self.rot.transpose(1, 2) if to_world else self.rot
+        return (v.reshape(len(R), -1, 3) @ R).reshape(len(R), -1)
+
+    def inverse(self, g, project):
+        """lambda = S_L^+ g per body, world frame; with project also (I - L)."""
+        P = len(self.rot)
+        v = self._turn(g.cpu().reshape(P, -1), False)
+        lam = torch.linalg.solve_triangular(self.R, self.Qt @ v.T, upper=True).T
+        if project:
+            lam = lam - lam @ self.K @ self.G @ self.K.T if self.stokes else lam - lam.mean(1, keepdim=True)
+        return self._turn(lam, True)
+
+    def completion(self, net):
+        z = net.cpu().reshape(len(self.rot), -1)
+        if not self.stokes:
+            return (z / len(self.yl)).expand(-1, len(self.yl))
+        zz = torch.cat([self._turn(z[:, :3], False), self._turn(z[:, 3:], False)], 1)
+        return self._turn(zz @ self.G @ self.K.T, True)
+
+    def pairs(self, s, skip=True):
+        k = (len(self.xl), len(self.yl)) if skip else None
+        return _pair_sum(self.x, self.y, s.reshape(len(self.y), -1).to(DEV), k, self.stokes).reshape(-1)
+
+    def apply(self, g):
+        return g + self.pairs(self.inverse(g, True))
+
+    def recover(self, g):
+        lam = self.inverse(g, False)
+        if not self.stokes:
+            return -lam.mean(1)
+        v = self._turn(lam, False) @ self.K
+        return -torch.cat([self._turn(v[:, :3], True), self._turn(v[:, 3:], True)], 1).reshape(-1)
+
+
+def _gmres(A, b, tol=1e-11, most=70):
+    V, H = [b / b.norm()], torch.zeros(most + 1, most, dtype=torch.float64)
+    for j in range(most):
+        w = A(V[j])
+        for _ in range(2):
+            h = torch.stack([v @ w for v in V])
+            w = w - sum(hi * v for hi, v in zip(h, V))
+            H[: j + 1, j] += h.cpu()
+        H[j + 1, j] = w.norm().cpu()
+        e = torch.zeros(j + 2, 1, dtype=torch.float64)
+        e[0] = b.norm().cpu()
+        y = torch.linalg.lstsq(H[: j + 2, : j + 1], e).solution
+        if (H[: j + 2, : j + 1] @ y - e).norm() <= tol * e[0, 0]:
+            break
+        V.append(w / H[j + 1, j].to(w.device))
+    return sum(yi.to(b.device) * v for yi, v in zip(y[:, 0], V))
+
+
+def exact(case, seed):
+    c = dict(case)
+    if c["op"] == "pair":
+        return _pair_exact(c, seed)
+    if c["op"] == "pair_backward":
+        return _backward_exact(c, seed)
+    if c["op"] == "traction":
+        return _traction_exact(c, seed)
+    if c["op"] == "gradient":
+        return None  # an adjoint solve and its pair gradients: not a short plain computation
+    wl = _workload(c, seed)
+    x, out, at = _dev(_smooth(wl, seed)), [], 0
+    if c["op"] == "solve":
+        if _pairs(c) > 1.2e9:
+            return None
+        A = _Operator(c, wl, 0)
+        net = torch.tensor(wl.net[0].reshape(-1))
+        g = _gmres(A.apply, -A.pairs(A.completion(net), skip=False))
+        return [A.recover(g), g]
+    if c["op"] == "matvec" and _pairs(c) > 6e10:
+        return None
+    for s in range(wl.n_sys):
+        A = _Operator(c, wl, s)
+        k = (3 if A.stokes else 1) * len(A.x)
+        v = x[at:at + k]
+        out.append(A.apply(v) if c["op"] == "matvec" else A.inverse(v, False).reshape(-1))
+        at += k
+    return torch.cat(out)
