@@ -24,6 +24,7 @@
 // workgroup per column, with the running sums in LDS.
 // Reductions add in a fixed order: results do not depend on timing.
 #include <algorithm>
+#include <type_traits>
 
 #include "mfs_internal.h"
 
@@ -247,6 +248,366 @@ __global__ __launch_bounds__(FB) void wy_apply_kernel(const double *__restrict__
     }
 }
 
+// ---------------------------------------------------------------------------
+// Steps for matrices whose rows fit one workgroup's registers (at most
+// QT * QR_MAX_RPT = 2560 rows; larger ones take the kernels above).
+//
+// A panel is a serial chain, column after column, so its time is latency:
+// panel_qr_kernel, which re-reads the panel from L2 in every column step, took
+// 0.27 ms per panel at 2400 rows, and wy_apply_kernel 69 us, its loads one
+// block of rows in flight per wave.  Here
+//  * the panel stays in registers, 16 columns of RPT rows in each of 512
+//    threads (a CU's 512 KB of registers against 0.3 MB of panel);
+//  * a column step is one pass, one barrier: the sums x_j . X_q over the rows
+//    below the diagonal give the norm, v_j . X_q (by scaling, with the row of the
+//    diagonal added) and the Gram entries of T together.  The columns rotate by
+//    one place per step, so the step is a loop body and not 16 unrolled copies
+//    (200 KB of code, run once, took 129 us per panel in instruction fetches);
+//  * the WY update has six blocks of rows in flight per wave;
+//  * one launch per panel: workgroup 0 updates the next panel's columns and
+//    factors them, the others update the rest meanwhile.
+// 2400 x 1200 (QR, Q and R^-1): 32.0 ms before, 9.1 ms now (a panel 41 us, a WY update
+// 38 us), plan creation 34.7 -> 11.7 ms.  sqrt and the divisions are not what a column
+// step waits for: through v_rsq_f64 and v_rcp_f64 a panel took the same 40 us.
+// ---------------------------------------------------------------------------
+constexpr int QT = 512;        // threads
+constexpr int QW = QT / 64;    // waves
+constexpr int QR_MAX_RPT = 5;  // rows per thread: 16 columns x 5 rows are 160 registers
+constexpr int QU = 6;          // row blocks in flight per wave of the WY update
+static_assert(NB == 16 && CT == 16, "one 16 x 16 tile of P, four lanes per panel column");
+
+struct QrShared {
+    double Pw[QW][NB][CT];  // partial V^T C of every wave
+    double W[NB][CT];
+    double Ts[NB][NB + 1];
+    double red[2][QW][NB];  // partial sums of a column step, double-buffered
+    double row[2][NB];      // the diagonal's row
+    double G[NB][NB + 1];
+    double tl[NB];
+};
+
+__device__ __forceinline__ double lane_value(double x, int lane) {  // lane: uniform
+    const int lo = __builtin_amdgcn_readlane(__double2loint(x), lane);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(x), lane);
+    return __hiloint2double(hi, lo);
+}
+
+// x of another lane of the row of 16: CTRL a DPP control that is a permutation of the row
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// a summed over a lane and its partner 32 (16) away in the lower half, b in the upper one
+template <int DIST>
+__device__ __forceinline__ double swap_add(double a, double b) {
+    typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+    uint2v lo, hi;
+    if constexpr (DIST == 32) {
+        lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+        hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+        hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    }
+    return __hiloint2double(hi.x, lo.x) + __hiloint2double(hi.y, lo.y);
+}
+
+// Sums of v[0..15] over the wave; lane l returns the sum of v[l / 4].  Every exchange halves
+// the values a lane still carries (8 + 4 + 2 + 1), the last two add the four lanes of a value.
+__device__ __forceinline__ double wave_sums16(double (&v)[16], int lane) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = swap_add<32>(v[q], v[q + 8]);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = swap_add<16>(v[q], v[q + 4]);
+    const bool up8 = (lane & 8) != 0, up4 = (lane & 4) != 0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const double send = up8 ? v[q] : v[q + 2], keep = up8 ? v[q + 2] : v[q];
+        v[q] = keep + dpp_move<0x128>(send);  // row_ror:8
+    }
+    const double send = up4 ? v[0] : v[1], keep = up4 ? v[1] : v[0];
+    double r = keep + dpp_move<0x141>(send);  // row_half_mirror: the other four of the eight
+    r += dpp_move<0xB1>(r);                   // quad_perm [1,0,3,2]
+    r += dpp_move<0x4E>(r);                   // quad_perm [2,3,0,1]
+    return r;
+}
+
+// Factors the panel at k0 (kb columns, rows k0..m-1 in registers: thread t holds rows
+// k0 + t + QT i) and forms T, as panel_qr_kernel does.  At step j the registers hold the
+// columns j, j+1, ..., 15, 0, ..., j-1, the last j of them reflectors already.
+template <int RPT>
+__device__ __forceinline__ void panel_registers(double *__restrict__ a, int m, int lda, int k0, int kb,
+                                                double *__restrict__ tau, double *__restrict__ T, QrShared &sh) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, ql = lane >> 2;
+    const unsigned rows = (unsigned)(m - k0);
+    double X[RPT][NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        const double *x = a + (int64_t)(k0 + (q < kb ? q : 0)) * lda + k0;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const unsigned r = t + QT * i;
+            X[i][q] = (r < rows && q < kb) ? x[r] : 0.0;
+        }
+    }
+#pragma unroll 1
+    for (int j = 0; j < NB; ++j) {
+        double d[NB];
+        {
+            const double x = t > j ? X[0][0] : 0.0;  // the rows at and above the diagonal are in the first block
+#pragma unroll
+            for (int q = 0; q < NB; ++q) d[q] = x * X[0][q];
+        }
+#pragma unroll
+        for (int i = 1; i < RPT; ++i)
+#pragma unroll
+            for (int q = 0; q < NB; ++q) d[q] += X[i][0] * X[i][q];
+        const int buf = j & 1;
+        if (t == j)
+#pragma unroll
+            for (int q = 0; q < NB; ++q) sh.row[buf][q] = X[0][q];
+        const double part = wave_sums16(d, lane);
+        if ((lane & 3) == 0) sh.red[buf][wave][ql] = part;
+        // one barrier per step: a buffer is written again two steps later, after the next
+        // step's barrier, which every thread reaches past its reads here
+        __syncthreads();
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < QW; ++w) s += sh.red[buf][w][ql];  // x_j . X_ql below the diagonal
+        const double rq = sh.row[buf][ql], alpha = sh.row[buf][0];
+        const double ss = lane_value(s, 0);
+        double tj = 0.0, scal = 1.0, beta = alpha;  // nothing below the diagonal: H_j = I, R_jj = A_jj
+        if (ss != 0.0) {
+            const double nrm = sqrt(alpha * alpha + ss);
+            beta = alpha >= 0.0 ? -nrm : nrm;  // no cancellation in alpha - beta
+            scal = 1.0 / (alpha - beta);
+            tj = (beta - alpha) / beta;
+        }
+        const double gq = scal * s + rq;  // v_j . X_ql, the diagonal's row included
+        const bool later = ql < NB - j;   // else X_ql is reflector ql - (NB - j)
+        const double wq = later ? tj * gq : 0.0;
+        if (wave == 0 && (lane & 3) == 0 && !later) sh.G[ql - (NB - j)][j] = gq;
+        if (t == 0) {
+            sh.tl[j] = tj;
+            if (j < kb) tau[k0 + j] = tj;
+        }
+        double v[RPT];
+        const double x0 = X[0][0];
+        v[0] = t > j ? x0 * scal : (t == j ? 1.0 : 0.0);
+#pragma unroll
+        for (int i = 1; i < RPT; ++i) v[i] = X[i][0] * scal;
+#pragma unroll
+        for (int q = 1; q < NB; ++q) {  // H_j applied to the later columns, each one place on
+            const double w = lane_value(wq, 4 * q);
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) X[i][q - 1] = X[i][q] - w * v[i];
+        }
+        X[0][NB - 1] = t > j ? v[0] : (t == j ? beta : x0);
+#pragma unroll
+        for (int i = 1; i < RPT; ++i) X[i][NB - 1] = v[i];
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q) {
+        double *x = a + (int64_t)(k0 + (q < kb ? q : 0)) * lda + k0;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const unsigned r = t + QT * i;
+            if (r < rows && q < kb) x[r] = X[i][q];
+        }
+    }
+    __syncthreads();  // G and tl complete
+    if (wave == 0 && lane < NB) {  // T column by column: lane i owns row i
+        const int i = lane;
+        for (int j = 0; j < NB; ++j) {
+            double v = 0.0;
+            if (j < kb) {
+                if (i < j) {
+                    double s = 0.0;
+                    for (int l = i; l < j; ++l) s += sh.Ts[i][l] * sh.G[l][j];
+                    v = -sh.tl[j] * s;
+                } else if (i == j) {
+                    v = sh.tl[j];
+                }
+            }
+            sh.Ts[i][j] = v;
+        }
+        for (int j = 0; j < NB; ++j) T[i * NB + j] = sh.Ts[i][j];
+    }
+}
+
+struct __attribute__((packed, aligned(8))) Rows4 { double v[4]; };  // four rows of a column
+
+// C[k0:m, cbase : min(cbase + 16, c1)] <- (I - V op(T) V^T) C, as wy_apply_kernel.  Lane l of a
+// 16-row block r0 holds rows r0 + 4 (l/16) + (0..3) of column l%16: the k slots of V^T C (MFMA u
+// takes row u of the four), and the D layout of V W when row i of the A operand there is row
+// 4 (i%4) + i/4 of the block.  Block b is wave b % QW's.
+template <bool TRANS>
+__device__ __forceinline__ void wy_update(const double *__restrict__ v, int m, int lda, int k0, int kb,
+                                          const double *__restrict__ T, double *__restrict__ cm, int ldc, int cbase,
+                                          int c1, QrShared &sh) {
+    const int t = threadIdx.x, lane = t & 63, q = lane >> 4, c16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int full = (m - k0) / 16;  // whole blocks; one more may hold the last rows
+    const int col = cbase + c16;
+    const bool cok = col < c1, vok = c16 < kb;
+    double *ccol = cm + (int64_t)(cok ? col : cbase) * ldc + k0 + 4 * q;
+    const double *vcol = v + (int64_t)(k0 + (vok ? c16 : 0)) * lda + k0 + 4 * q;
+    for (int e = t; e < NB * NB; e += QT) sh.Ts[e / NB][e % NB] = T[e];
+    // 1. P = V^T C; a block past the last whole one reads the last whole one and counts as zero
+    doublex4 acc[2] = {};
+    auto add = [&](const Rows4 &c, const Rows4 &x, int b) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            double y = vok ? x.v[u] : 0.0;
+            if (b == 0) {  // the unit lower triangle
+                const int r = 4 * q + u;
+                y = (r < c16 || !vok) ? 0.0 : (r == c16 ? 1.0 : y);
+            }
+            acc[u & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(y, c.v[u], acc[u & 1], 0, 0, 0);
+        }
+    };
+    for (int b0 = wave; b0 < full; b0 += QW * QU) {
+        Rows4 c[QU], x[QU];
+#pragma unroll
+        for (int i = 0; i < QU; ++i) {
+            const int b = min(b0 + QW * i, full - 1);
+            c[i] = *reinterpret_cast<const Rows4 *>(ccol + 16 * b);
+            x[i] = *reinterpret_cast<const Rows4 *>(vcol + 16 * b);
+        }
+#pragma unroll
+        for (int i = 0; i < QU; ++i)
+            if (b0 + QW * i < full) add(c[i], x[i], b0 + QW * i);
+    }
+    if (k0 + 16 * full < m && wave == full % QW) {
+        Rows4 c, x;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = k0 + 16 * full + 4 * q + u < m;
+            c.v[u] = ok ? ccol[16 * full + u] : 0.0;
+            x.v[u] = ok ? vcol[16 * full + u] : 0.0;
+        }
+        add(c, x, full);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sh.Pw[wave][q + 4 * r][c16] = acc[0][r] + acc[1][r];
+    __syncthreads();
+    if (t < NB * CT) {  // P summed over the waves in order
+        const int i = t / CT, j = t % CT;
+        double p = sh.Pw[0][i][j];
+#pragma unroll
+        for (int w = 1; w < QW; ++w) p += sh.Pw[w][i][j];
+        sh.Pw[0][i][j] = p;
+    }
+    __syncthreads();
+    if (t < NB * CT) {  // 2. W = op(T) P
+        const int i = t / CT, j = t % CT;
+        double s = 0.0;
+        if (TRANS) {
+            for (int l = 0; l <= i; ++l) s += sh.Ts[l][i] * sh.Pw[0][l][j];
+        } else {
+            for (int l = i; l < NB; ++l) s += sh.Ts[i][l] * sh.Pw[0][l][j];
+        }
+        sh.W[i][j] = s;
+    }
+    __syncthreads();
+    // 3. C -= V W
+    double wv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) wv[u] = sh.W[4 * u + q][c16];
+    const int rho = 4 * (c16 & 3) + (c16 >> 2);
+    const double *vk[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) vk[u] = v + (int64_t)(k0 + min(4 * u + q, kb - 1)) * lda + k0 + rho;
+    auto product = [&](const double (&x)[4], int b) {
+        doublex4 o = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = 4 * u + q;
+            double y = k < kb ? x[u] : 0.0;
+            if (b == 0) y = (rho < k || k >= kb) ? 0.0 : (rho == k ? 1.0 : y);
+            o = __builtin_amdgcn_mfma_f64_16x16x4f64(y, wv[u], o, 0, 0, 0);
+        }
+        return o;
+    };
+    for (int b0 = wave; b0 < full; b0 += QW * QU) {
+        Rows4 c[QU];
+        double x[QU][4];
+#pragma unroll
+        for (int i = 0; i < QU; ++i) {
+            const int b = min(b0 + QW * i, full - 1);
+            c[i] = *reinterpret_cast<const Rows4 *>(ccol + 16 * b);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[i][u] = vk[u][16 * b];
+        }
+#pragma unroll
+        for (int i = 0; i < QU; ++i) {
+            const int b = b0 + QW * i;
+            if (b >= full) continue;
+            const doublex4 o = product(x[i], b);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) c[i].v[u] -= o[u];
+            if (cok) *reinterpret_cast<Rows4 *>(ccol + 16 * b) = c[i];
+        }
+    }
+    if (k0 + 16 * full < m && wave == full % QW) {
+        double x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = k0 + 16 * full + rho < m ? vk[u][16 * full] : 0.0;
+        const doublex4 o = product(x, full);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (cok && k0 + 16 * full + 4 * q + u < m) ccol[16 * full + u] -= o[u];
+    }
+}
+
+// First panel.
+template <int RPT>
+__global__ __launch_bounds__(QT) void qr_first_kernel(double *__restrict__ A, int m, int64_t stride, int kb,
+                                                      double *__restrict__ tau, int n, double *__restrict__ Tp) {
+    __shared__ QrShared sh;
+    const int b = blockIdx.x;
+    panel_registers<RPT>(A + (int64_t)b * stride, m, m, 0, kb, tau + (int64_t)b * n, Tp + (int64_t)b * NB * NB, sh);
+}
+
+// One step of the QR: the panel at k0 (factored, T in Tp) is applied to the columns after it,
+// one workgroup per 16 columns; workgroup 0, whose columns are the next panel, factors them.
+template <int RPT>
+__global__ __launch_bounds__(QT) void qr_step_kernel(double *__restrict__ A, int m, int64_t stride, int k0, int n,
+                                                     const double *__restrict__ Tp, double *__restrict__ tau,
+                                                     double *__restrict__ Tnext) {
+    __shared__ QrShared sh;
+    const int b = blockIdx.y, c = k0 + NB + (int)blockIdx.x * CT;
+    double *a = A + (int64_t)b * stride;
+    wy_update<true>(a, m, m, k0, NB, Tp + (int64_t)b * NB * NB, a, m, c, n, sh);
+    if (blockIdx.x != 0) return;  // uniform over the workgroup
+    __syncthreads();              // the updated columns are read back in the panel's layout
+    panel_registers<RPT>(a, m, m, c, min(NB, n - c), tau + (int64_t)b * n, Tnext + (int64_t)b * NB * NB, sh);
+}
+
+// Q <- (I - V T V^T) Q on rows k0..m-1 of columns k0..n-1.
+__global__ __launch_bounds__(QT) void q_step_kernel(const double *__restrict__ A, int m, int64_t stride_a, int k0, int kb,
+                                                    const double *__restrict__ Tp, double *__restrict__ Q,
+                                                    int64_t stride_q, int n) {
+    __shared__ QrShared sh;
+    const int b = blockIdx.y;
+    wy_update<false>(A + (int64_t)b * stride_a, m, m, k0, kb, Tp + (int64_t)b * NB * NB, Q + (int64_t)b * stride_q, m,
+                     k0 + (int)blockIdx.x * CT, n, sh);
+}
+
+template <class F>
+void with_rows(int rows, F &&f) {  // f(integral_constant<RPT>) with RPT = ceil(rows / QT)
+    switch ((rows + QT - 1) / QT) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 3: f(std::integral_constant<int, 3>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        default: f(std::integral_constant<int, 5>{}); break;
+    }
+}
+
 // Q = [I_n; 0] (column-major m x n, leading dimension m)
 __global__ void identity_kernel(double *__restrict__ Q, int m, int n, int64_t stride, int64_t total) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -329,21 +690,36 @@ int qr_inverse_batched(int batch, double *A, int m, int n, int64_t stride_a, dou
     double *colsq = scratch + (size_t)batch * n;      // [batch][2][n]
     double *Tall = scratch + (size_t)batch * n * 3;  // T of panel p: Tall + p * batch * NB * NB
     const int panels = (n + NB - 1) / NB;
-    for (int p = 0; p < panels; ++p) {
-        const int k0 = p * NB, kb = std::min(NB, n - k0);
-        double *Tp = Tall + (size_t)p * batch * NB * NB;
-        panel_qr_kernel<<<batch, PT, 0, s>>>(A, m, m, stride_a, k0, kb, tau, n, Tp);
-        if (k0 + kb < n)
-            wy_apply_kernel<true><<<dim3((n - k0 - kb + CT - 1) / CT, batch), FB, 0, s>>>(
-                A, m, m, stride_a, k0, kb, Tp, A, m, stride_a, k0 + kb, n);
+    const bool in_registers = m <= QT * QR_MAX_RPT;  // else the panel does not fit a workgroup's registers
+    auto panel_T = [&](int p) { return Tall + (size_t)p * batch * NB * NB; };
+    if (in_registers) {
+        with_rows(m, [&](auto R) {
+            qr_first_kernel<R.value><<<batch, QT, 0, s>>>(A, m, stride_a, std::min(NB, n), tau, n, panel_T(0));
+        });
+        for (int p = 0; p + 1 < panels; ++p)
+            with_rows(m - (p + 1) * NB, [&](auto R) {
+                qr_step_kernel<R.value><<<dim3(panels - p - 1, batch), QT, 0, s>>>(A, m, stride_a, p * NB, n, panel_T(p),
+                                                                                  tau, panel_T(p + 1));
+            });
+    } else {
+        for (int p = 0; p < panels; ++p) {
+            const int k0 = p * NB, kb = std::min(NB, n - k0);
+            panel_qr_kernel<<<batch, PT, 0, s>>>(A, m, m, stride_a, k0, kb, tau, n, panel_T(p));
+            if (k0 + kb < n)
+                wy_apply_kernel<true><<<dim3((n - k0 - kb + CT - 1) / CT, batch), FB, 0, s>>>(
+                    A, m, m, stride_a, k0, kb, panel_T(p), A, m, stride_a, k0 + kb, n);
+        }
     }
     MFS_HIP_TRY(hipGetLastError());
     const int64_t total = (int64_t)batch * m * n;
     identity_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(Q, m, n, stride_q, total);
     for (int p = panels - 1; p >= 0; --p) {
         const int k0 = p * NB, kb = std::min(NB, n - k0);
-        wy_apply_kernel<false><<<dim3((n - k0 + CT - 1) / CT, batch), FB, 0, s>>>(
-            A, m, m, stride_a, k0, kb, Tall + (size_t)p * batch * NB * NB, Q, m, stride_q, k0, n);
+        const dim3 grid((n - k0 + CT - 1) / CT, batch);
+        if (in_registers)
+            q_step_kernel<<<grid, QT, 0, s>>>(A, m, stride_a, k0, kb, panel_T(p), Q, stride_q, n);
+        else
+            wy_apply_kernel<false><<<grid, FB, 0, s>>>(A, m, m, stride_a, k0, kb, panel_T(p), Q, m, stride_q, k0, n);
     }
     MFS_HIP_TRY(hipGetLastError());
     upper_inverse_kernel<<<dim3(n, batch), FB, (size_t)n * sizeof(double), s>>>(A, n, m, stride_a, X, n, stride_x,
