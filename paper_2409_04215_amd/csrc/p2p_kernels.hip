@@ -65,21 +65,65 @@ struct Src4 {
     SrcS32 s[4];
 };
 
-// One Stokes source against the lane's TPL targets, FP32 (eq. (stokeslet) without 1/(8 pi mu)).
-template <int TPL>
-__device__ __forceinline__ void stokes_pair(const float (&xr)[TPL][3], const float4 y, const float4 f,
-                                            float (&p)[TPL][3]) {
+// U Stokes sources against the lane's TPL targets, FP32 (eq. (stokeslet) without 1/(8 pi mu)).
+template <int TPL, int U>
+__device__ __forceinline__ void stokes_pairs(const float (&xr)[TPL][3], const SrcS32 *s, float (&p)[TPL][3]) {
+    float d[U][TPL][3], ri[U][TPL];
 #pragma unroll
-    for (int t = 0; t < TPL; ++t) {
-        const float d0 = xr[t][0] - y.x, d1 = xr[t][1] - y.y, d2 = xr[t][2] - y.z;
-        const float r2 = __builtin_fmaf(d2, d2, __builtin_fmaf(d1, d1, d0 * d0));
-        const float ri = __builtin_amdgcn_rsqf(r2);
-        const float df = __builtin_fmaf(d2, f.z, __builtin_fmaf(d1, f.y, d0 * f.x));
-        const float sc = df * (ri * ri);
-        p[t][0] = __builtin_fmaf(ri, __builtin_fmaf(sc, d0, f.x), p[t][0]);
-        p[t][1] = __builtin_fmaf(ri, __builtin_fmaf(sc, d1, f.y), p[t][1]);
-        p[t][2] = __builtin_fmaf(ri, __builtin_fmaf(sc, d2, f.z), p[t][2]);
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < TPL; ++t) {
+            const float4 y = s[u].pos;
+            float *e = d[u][t];
+            e[0] = xr[t][0] - y.x;
+            e[1] = xr[t][1] - y.y;
+            e[2] = xr[t][2] - y.z;
+            ri[u][t] = __builtin_fmaf(e[2], e[2], __builtin_fmaf(e[1], e[1], e[0] * e[0]));
+        }
+    rsq_cluster_begin();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < TPL; ++t) ri[u][t] = __builtin_amdgcn_rsqf(ri[u][t]);
+    rsq_cluster_end();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < TPL; ++t) {
+            const float4 f = s[u].str;
+            const float *e = d[u][t], r = ri[u][t];
+            const float df = __builtin_fmaf(e[2], f.z, __builtin_fmaf(e[1], f.y, e[0] * f.x));
+            const float sc = df * (r * r);
+            p[t][0] = __builtin_fmaf(r, __builtin_fmaf(sc, e[0], f.x), p[t][0]);
+            p[t][1] = __builtin_fmaf(r, __builtin_fmaf(sc, e[1], f.y), p[t][1]);
+            p[t][2] = __builtin_fmaf(r, __builtin_fmaf(sc, e[2], f.z), p[t][2]);
+        }
+}
+
+// U Laplace sources (LDS) against the lane's TPL targets, FP32 (1/r without 1/(4 pi)).
+template <int TPL, int U>
+__device__ __forceinline__ void laplace_pairs(const float (&xr)[TPL][3], const float4 *s, float (&p)[TPL]) {
+    float q[U], ri[U][TPL];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float4 y = s[u];
+        q[u] = y.w;
+#pragma unroll
+        for (int t = 0; t < TPL; ++t) {
+            const float d0 = xr[t][0] - y.x, d1 = xr[t][1] - y.y, d2 = xr[t][2] - y.z;
+            ri[u][t] = __builtin_fmaf(d2, d2, __builtin_fmaf(d1, d1, d0 * d0));
+        }
     }
+    rsq_cluster_begin();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < TPL; ++t) ri[u][t] = __builtin_amdgcn_rsqf(ri[u][t]);
+    rsq_cluster_end();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int t = 0; t < TPL; ++t) p[t] = __builtin_fmaf(q[u], ri[u][t], p[t]);
 }
 
 // This wave's contiguous quarter [j0, j1) of the source range [b0, b1).
@@ -171,10 +215,9 @@ __device__ __forceinline__ void mixed_item(const KernelArgs &a, const P2PItem it
                 int k = 0;
                 for (; k + 4 <= n; k += 4) {
                     const Src4 q = *reinterpret_cast<const Src4 *>(ps + k);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) stokes_pair<TPL>(xr, q.s[u].pos, q.s[u].str, p);
+                    stokes_pairs<TPL, 4>(xr, q.s, p);
                 }
-                for (; k < n; ++k) stokes_pair<TPL>(xr, ps[k].pos, ps[k].str, p);
+                for (; k < n; ++k) stokes_pairs<TPL, 1>(xr, ps + k, p);
 #pragma unroll
                 for (int t = 0; t < TPL; ++t) {
                     acc[t][0] += use[t] ? (double)p[t][0] : 0.0;
@@ -197,16 +240,9 @@ __device__ __forceinline__ void mixed_item(const KernelArgs &a, const P2PItem it
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll 8
-                for (int k = 0; k < cnt; ++k) {
-                    const float4 y = slot[k];
-#pragma unroll
-                    for (int t = 0; t < TPL; ++t) {
-                        const float d0 = xr[t][0] - y.x, d1 = xr[t][1] - y.y, d2 = xr[t][2] - y.z;
-                        const float r2 = __builtin_fmaf(d2, d2, __builtin_fmaf(d1, d1, d0 * d0));
-                        p[t] = __builtin_fmaf(y.w, __builtin_amdgcn_rsqf(r2), p[t]);
-                    }
-                }
+                int k = 0;
+                for (; k + 8 <= cnt; k += 8) laplace_pairs<TPL, 8>(xr, slot + k, p);
+                for (; k < cnt; ++k) laplace_pairs<TPL, 1>(xr, slot + k, p);
 #pragma unroll
                 for (int t = 0; t < TPL; ++t) acc[t][0] += use[t] ? (double)p[t] : 0.0;
                 __builtin_amdgcn_wave_barrier();  // the next run's stores follow this run's reads
