@@ -15,8 +15,7 @@
 // partial sums are added in wave order through LDS.  These fields are
 // evaluated after a solve (surface traction, pressure, residual checks), not
 // inside GMRES.
-#include "device_math.h"
-#include "mfs_internal.h"
+#include "pair_math.h"
 
 namespace mfs {
 
@@ -39,10 +38,52 @@ struct FieldArgs {
 };
 
 template <bool MIXED, int FLD>
+struct FieldSource { typedef typename Records<MIXED>::S T; };
+template <bool MIXED>
+struct FieldSource<MIXED, MFS_FIELD_LAPLACE_GRADIENT> { typedef typename Records<MIXED>::L T; };
+
+// U sources against the lane's target, without the constant factors
+template <bool MIXED, int FLD, int U, class R, int DIM>
+__device__ __forceinline__ void field_pairs(const R (&xr)[3], const R (&nv)[3],
+                                            const typename FieldSource<MIXED, FLD>::T *src, R (&p)[DIM]) {
+    R d[U][3], ri[U], f[U][3], q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        R y[3];
+        if constexpr (FLD == MFS_FIELD_LAPLACE_GRADIENT) source(src[u], y, q[u]);
+        else source(src[u], y, f[u]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) d[u][c] = xr[c] - y[c];
+        ri[u] = d[u][0] * d[u][0] + d[u][1] * d[u][1] + d[u][2] * d[u][2];
+    }
+    rsqrt_all(ri);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const R ri2 = ri[u] * ri[u], ri3 = ri[u] * ri2;
+        if constexpr (FLD == MFS_FIELD_LAPLACE_GRADIENT) {
+            const R c = q[u] * ri3;
+#pragma unroll
+            for (int e = 0; e < 3; ++e) p[e] += c * d[u][e];
+        } else {
+            const R df = d[u][0] * f[u][0] + d[u][1] * f[u][1] + d[u][2] * f[u][2];
+            if constexpr (FLD == MFS_FIELD_PRESSURE) {
+                p[0] += df * ri3;
+            } else {
+                const R c = (d[u][0] * nv[0] + d[u][1] * nv[1] + d[u][2] * nv[2]) * df * ri3 * ri2;
+#pragma unroll
+                for (int e = 0; e < 3; ++e) p[e] += c * d[u][e];
+            }
+        }
+    }
+}
+
+template <bool MIXED, int FLD>
 __global__ __launch_bounds__(BLOCK) void field_kernel(FieldArgs a, const void *__restrict__ trg_off_v,
                                                       const void *__restrict__ src_v) {
-    typedef typename std::conditional<MIXED, float, double>::type R;
+    typedef typename Records<MIXED>::R R;
     constexpr int DIM = FLD == MFS_FIELD_PRESSURE ? 1 : 3;
+    constexpr int U = MIXED ? 4 : 2;  // sources per step
+    const auto *src = reinterpret_cast<const typename FieldSource<MIXED, FLD>::T *>(src_v);
     __shared__ double lds[(WAVES - 1) * 3 * 64];
     const P2PItem it = a.items[blockIdx.x];
     const int lane = threadIdx.x & 63;
@@ -75,51 +116,11 @@ __global__ __launch_bounds__(BLOCK) void field_kernel(FieldArgs a, const void *_
         const int j0 = min(s0 + wv * qn, s1), j1 = min(j0 + qn, s1);
         for (int jb = j0; jb < j1; jb += FLUSH) {
             const int je = min(jb + FLUSH, j1);
-            R p0 = 0, p1 = 0, p2 = 0;
-#pragma unroll 2
-            for (int j = jb; j < je; ++j) {
-                R y0, y1, y2, f0 = 0, f1 = 0, f2 = 0, q = 0;
-                if (FLD == MFS_FIELD_LAPLACE_GRADIENT) {
-                    if (MIXED) {
-                        const float4 sj = reinterpret_cast<const float4 *>(src_v)[j];
-                        y0 = sj.x; y1 = sj.y; y2 = sj.z; q = sj.w;
-                    } else {
-                        const SrcL64 &sj = reinterpret_cast<const SrcL64 *>(src_v)[j];
-                        y0 = sj.v[0]; y1 = sj.v[1]; y2 = sj.v[2]; q = sj.v[3];
-                    }
-                } else if (MIXED) {
-                    const SrcS32 &sj = reinterpret_cast<const SrcS32 *>(src_v)[j];
-                    y0 = sj.pos.x; y1 = sj.pos.y; y2 = sj.pos.z;
-                    f0 = sj.str.x; f1 = sj.str.y; f2 = sj.str.z;
-                } else {
-                    const SrcS64 &sj = reinterpret_cast<const SrcS64 *>(src_v)[j];
-                    y0 = sj.pos[0]; y1 = sj.pos[1]; y2 = sj.pos[2];
-                    f0 = sj.str[0]; f1 = sj.str[1]; f2 = sj.str[2];
-                }
-                const R d0 = xr[0] - y0, d1 = xr[1] - y1, d2 = xr[2] - y2;
-                const R r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                R ri;
-                if (MIXED) ri = __builtin_amdgcn_rsqf((float)r2);
-                else ri = (R)rsqrt_f64((double)r2);
-                const R ri2 = ri * ri;
-                const R ri3 = ri * ri2;
-                if (FLD == MFS_FIELD_PRESSURE) {
-                    p0 += (d0 * f0 + d1 * f1 + d2 * f2) * ri3;
-                } else if (FLD == MFS_FIELD_TRACTION) {
-                    const R c = (d0 * nv[0] + d1 * nv[1] + d2 * nv[2]) * (d0 * f0 + d1 * f1 + d2 * f2) * ri3 * ri2;
-                    p0 += c * d0;
-                    p1 += c * d1;
-                    p2 += c * d2;
-                } else {
-                    const R c = q * ri3;
-                    p0 += c * d0;
-                    p1 += c * d1;
-                    p2 += c * d2;
-                }
-            }
-            acc[0] += use ? (double)p0 : 0.0;
-            acc[1] += use ? (double)p1 : 0.0;
-            acc[2] += use ? (double)p2 : 0.0;
+            R p[DIM] = {};
+            int j = jb;
+            for (; j + U <= je; j += U) field_pairs<MIXED, FLD, U>(xr, nv, src + j, p);
+            for (; j < je; ++j) field_pairs<MIXED, FLD, 1>(xr, nv, src + j, p);
+            for (int c = 0; c < DIM; ++c) acc[c] += use ? (double)p[c] : 0.0;
         }
     }
     // waves 1..3 hand their partial sums to wave 0, which adds them in wave order

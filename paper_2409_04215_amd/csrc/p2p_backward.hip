@@ -19,8 +19,7 @@
 // (wave-uniform loop, scalar loads, SGPR operands), the partial gradients added
 // in wave order through LDS, same-body handling and mixed FP32-pair /
 // FP64-accumulation precision exactly as there.
-#include "device_math.h"
-#include "mfs_internal.h"
+#include "pair_math.h"
 
 namespace mfs {
 
@@ -43,14 +42,65 @@ struct GradArgs {
     int accumulate;
 };
 
-template <class T>
-struct Vec3 { T x, y, z; };
+// U Stokes sources: with c = 1/r^3, the pair's gradient is
+//   c (-(w.s) - 3 (w.d)(s.d) / r^2) d + c (w.d) s + c (s.d) w.
+// The coefficients of w are added up in pw and multiplied once per run, so a pair takes 30
+// operations and a 1/sqrt.
+template <bool MIXED, int U, class R>
+__device__ __forceinline__ void stokes_grad(const R (&xr)[3], const R (&w)[3], const typename Records<MIXED>::S *src,
+                                            R (&p)[3], R &pw) {
+    R d[U][3], ri[U], s[U][3];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        R y[3];
+        source(src[u], y, s[u]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) d[u][c] = xr[c] - y[c];
+        ri[u] = d[u][0] * d[u][0] + d[u][1] * d[u][1] + d[u][2] * d[u][2];
+    }
+    rsqrt_all(ri);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const R ri2 = ri[u] * ri[u], c3 = ri[u] * ri2;
+        const R ws = w[0] * s[u][0] + w[1] * s[u][1] + w[2] * s[u][2];
+        const R wd = w[0] * d[u][0] + w[1] * d[u][1] + w[2] * d[u][2];
+        const R sd = s[u][0] * d[u][0] + s[u][1] * d[u][1] + s[u][2] * d[u][2];
+        const R k = c3 * (R(-3) * (wd * sd * ri2) - ws), a = c3 * wd;
+        pw += c3 * sd;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) p[c] += k * d[u][c] + a * s[u][c];
+    }
+}
+
+// U Laplace sources: p += q d / r^3 (the factor -w follows once per run)
+template <bool MIXED, int U, class R>
+__device__ __forceinline__ void laplace_grad(const R (&xr)[3], const typename Records<MIXED>::L *src, R (&p)[3]) {
+    R d[U][3], ri[U], q[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        R y[3];
+        source(src[u], y, q[u]);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) d[u][c] = xr[c] - y[c];
+        ri[u] = d[u][0] * d[u][0] + d[u][1] * d[u][1] + d[u][2] * d[u][2];
+    }
+    rsqrt_all(ri);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const R c = q[u] * ri[u] * (ri[u] * ri[u]);
+#pragma unroll
+        for (int e = 0; e < 3; ++e) p[e] += c * d[u][e];
+    }
+}
 
 template <bool MIXED>
 __global__ __launch_bounds__(BLOCK) void p2p_grad_kernel(GradArgs a, const void *__restrict__ lane_off_v,
                                                          const void *__restrict__ srcS_v,
                                                          const void *__restrict__ srcL_v) {
-    typedef typename std::conditional<MIXED, float, double>::type R;
+    typedef typename Records<MIXED>::R R;
+    constexpr int U = MIXED ? 4 : 2;  // sources per step
+    const auto *src_s = reinterpret_cast<const typename Records<MIXED>::S *>(srcS_v);
+    const auto *src_l = reinterpret_cast<const typename Records<MIXED>::L *>(srcL_v);
     __shared__ double lds[(WAVES - 1) * 3 * 64];
     const P2PItem it = a.items[blockIdx.x];
     const bool stokes = it.kind == MFS_STOKES;
@@ -88,60 +138,18 @@ __global__ __launch_bounds__(BLOCK) void p2p_grad_kernel(GradArgs a, const void 
         const int j0 = min(s0 + wv * qn, s1), j1 = min(j0 + qn, s1);
         for (int jb = j0; jb < j1; jb += FLUSH) {
             const int je = min(jb + FLUSH, j1);
-            R p0 = 0, p1 = 0, p2 = 0;
+            R p[3] = {R(0), R(0), R(0)}, pw = R(0);
+            int j = jb;
             if (stokes) {
-#pragma unroll 2
-                for (int j = jb; j < je; ++j) {
-                    R y0, y1, y2, s0, s1, s2;
-                    if (MIXED) {
-                        const SrcS32 &sj = reinterpret_cast<const SrcS32 *>(srcS_v)[j];
-                        y0 = sj.pos.x; y1 = sj.pos.y; y2 = sj.pos.z;
-                        s0 = sj.str.x; s1 = sj.str.y; s2 = sj.str.z;
-                    } else {
-                        const SrcS64 &sj = reinterpret_cast<const SrcS64 *>(srcS_v)[j];
-                        y0 = sj.pos[0]; y1 = sj.pos[1]; y2 = sj.pos[2];
-                        s0 = sj.str[0]; s1 = sj.str[1]; s2 = sj.str[2];
-                    }
-                    const R d0 = xr[0] - y0, d1 = xr[1] - y1, d2 = xr[2] - y2;
-                    const R r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                    R ri;
-                    if (MIXED) ri = __builtin_amdgcn_rsqf((float)r2);
-                    else ri = (R)rsqrt_f64((double)r2);
-                    const R ri2 = ri * ri;
-                    const R c3 = ri * ri2;
-                    const R ws = w[0] * s0 + w[1] * s1 + w[2] * s2;
-                    const R wd = w[0] * d0 + w[1] * d1 + w[2] * d2;
-                    const R sd = s0 * d0 + s1 * d1 + s2 * d2;
-                    const R k = -ws - R(3) * wd * sd * ri2;
-                    p0 += c3 * (k * d0 + wd * s0 + sd * w[0]);
-                    p1 += c3 * (k * d1 + wd * s1 + sd * w[1]);
-                    p2 += c3 * (k * d2 + wd * s2 + sd * w[2]);
-                }
+                for (; j + U <= je; j += U) stokes_grad<MIXED, U>(xr, w, src_s + j, p, pw);
+                for (; j < je; ++j) stokes_grad<MIXED, 1>(xr, w, src_s + j, p, pw);
+                for (int c = 0; c < 3; ++c) p[c] += pw * w[c];
             } else {
-#pragma unroll 4
-                for (int j = jb; j < je; ++j) {
-                    R y0, y1, y2, q;
-                    if (MIXED) {
-                        const float4 sj = reinterpret_cast<const float4 *>(srcL_v)[j];
-                        y0 = sj.x; y1 = sj.y; y2 = sj.z; q = sj.w;
-                    } else {
-                        const SrcL64 &sj = reinterpret_cast<const SrcL64 *>(srcL_v)[j];
-                        y0 = sj.v[0]; y1 = sj.v[1]; y2 = sj.v[2]; q = sj.v[3];
-                    }
-                    const R d0 = xr[0] - y0, d1 = xr[1] - y1, d2 = xr[2] - y2;
-                    const R r2 = d0 * d0 + d1 * d1 + d2 * d2;
-                    R ri;
-                    if (MIXED) ri = __builtin_amdgcn_rsqf((float)r2);
-                    else ri = (R)rsqrt_f64((double)r2);
-                    const R c = -w[0] * q * ri * ri * ri;
-                    p0 += c * d0;
-                    p1 += c * d1;
-                    p2 += c * d2;
-                }
+                for (; j + U <= je; j += U) laplace_grad<MIXED, U>(xr, src_l + j, p);
+                for (; j < je; ++j) laplace_grad<MIXED, 1>(xr, src_l + j, p);
+                for (int c = 0; c < 3; ++c) p[c] *= -w[0];
             }
-            acc[0] += use ? (double)p0 : 0.0;
-            acc[1] += use ? (double)p1 : 0.0;
-            acc[2] += use ? (double)p2 : 0.0;
+            for (int c = 0; c < 3; ++c) acc[c] += use ? (double)p[c] : 0.0;
         }
     }
     // waves 1..3 hand their partial gradients to wave 0, which adds them in wave order
