@@ -148,6 +148,29 @@ int generate_p2p_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
     return MFS_OK;
 }
 
+// The least number of work items of a pair-sum launch of this size.  A launch holds about 2048
+// workgroups at a time, so with n items the last round idles about 2048 / 2n of the chip's
+// time T, and an item costs about 8 us of a workgroup's beside its pairs (set-up, the sum over
+// its waves, its part of the slice sums); the sum of both is least at n = 2048 sqrt(T / 16 us).
+// Measured (matvec, us, at 2048 / 4096 / 8192 / 16384 / 32768 items): 50 bodies (T = 0.16 ms)
+// 206 / 197 / 203 / 214 / 212, 80 bodies (0.4 ms) 471 / 452 / 443 / 449 / 481, 400 bodies
+// (18 ms) 18700 / 18760 / 17830 / 17220 / 17020.  T from 2.8e12 Stokes or twice as many
+// Laplace pairs per second, and of the largest system alone: the items of a batch differ in
+// size and are handed out largest first, so the small systems fill the last round (12 systems
+// of 17 to 62 bodies: 529 us at 5500 items, 565 at 10000).
+int default_min_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
+                      const int64_t *body_src_ptr, const int32_t *kind_of_body, int kind_all, int most) {
+    double us = 0.0;
+    for (int64_t sy = 0; sy < n_sys; ++sy) {
+        const int64_t b0 = sys_body_ptr[sy], b1 = sys_body_ptr[sy + 1];
+        if (b1 == b0) continue;
+        const int kind = kind_of_body ? kind_of_body[b0] : kind_all;
+        us = std::max(us, (double)(body_trg_ptr[b1] - body_trg_ptr[b0]) * (double)(body_src_ptr[b1] - body_src_ptr[b0]) /
+                              (kind == MFS_STOKES ? 2.8e6 : 5.6e6));
+    }
+    return (int)std::min((double)most, std::max(2048.0, 2048.0 * std::sqrt(us / 16.0)));
+}
+
 int build_p2p_items(P2PPlan &pp, int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                     const int64_t *body_src_ptr, const int64_t *out_ptr, const int32_t *kind_of_body, double mu,
                     int tpl, int min_items, hipStream_t s) {
@@ -191,10 +214,11 @@ struct Layout {
     uint64_t last_use = 0;
 };
 
-// launch shape of the standalone pair sums (one target per lane, at least this many
-// work items: a source split keeps the chip busy for single suspensions of a few
-// hundred bodies, as the plans' autotuner finds)
+// launch shape of the standalone pair sums: one target per lane, default_min_items up to this
+// many (the allocation-free call holds the items and slices of that many)
 constexpr int kStandaloneMinItems = 16384;
+// and of the plans' pair sums until they are tuned or set
+constexpr int kPlanMinItems = 65536;
 
 struct Workspace {
     DevBuf centre, trg_off, src_ops, partial;
@@ -293,8 +317,10 @@ int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_s
     std::vector<int64_t> out_ptr(nb + 1);
     for (int64_t b = 0; b <= nb; ++b) out_ptr[b] = dim * body_trg_ptr[b];
     std::vector<int32_t> kob(std::max<int64_t>(1, nb), kind);
+    const int min_items = default_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, kind,
+                                            kStandaloneMinItems);
     MFS_TRY(build_p2p_items(l->pp, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, out_ptr.data(), kob.data(), mu, 1,
-                            kStandaloneMinItems, s));
+                            min_items, s));
     l->last_use = ++ws.clock;
     *out = l.get();
     ws.layouts.push_back(std::move(l));
@@ -1042,7 +1068,9 @@ int p2p_stokes_noalloc(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
     int64_t n_items = 0;
     int n_split = 1;
     MFS_TRY(generate_p2p_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, 3, nullptr, MFS_STOKES, mu, 1,
-                               kStandaloneMinItems, h.items, h.work, h.order, h.sorted, kNoAllocMaxItems, &n_items,
+                               default_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, MFS_STOKES,
+                                                 kStandaloneMinItems),
+                               h.items, h.work, h.order, h.sorted, kNoAllocMaxItems, &n_items,
                                &n_split));
     // scratch layout (256-byte aligned pieces)
     const bool f32 = prec == MFS_MIXED;
@@ -1306,7 +1334,9 @@ int mfs_plan_create(mfs_plan *out, const mfs_plan_desc *d, void *stream) {
     // pair-sum items, forward (targets = collocation points) and transposed (targets = proxies)
     {
         std::vector<int64_t> src_row(p->src_row), trg_row(p->trg_row);
-        const int min_items = 2048;
+        const int min_items = default_min_items(p->n_sys, p->sys_body_ptr.data(), trg_row.data(), src_row.data(),
+                                                p->kind.data(), 0, kPlanMinItems);
+        p->tuned_min_items = min_items;
         MFS_TRY(build_p2p_items(p->p2p_fwd, p->n_sys, p->sys_body_ptr.data(), trg_row.data(), src_row.data(),
                                 p->gam_off.data(), p->kind.data(), p->mu, 1, min_items, s));
         MFS_TRY(build_p2p_items(p->p2p_tr, p->n_sys, p->sys_body_ptr.data(), src_row.data(), trg_row.data(),
@@ -2302,7 +2332,10 @@ extern "C" int mfs_surface_residual(mfs_plan p, const double *sigma, const doubl
     std::vector<int64_t> src_row(p->src_row);
     P2PPlan pp;
     MFS_TRY(build_p2p_items(pp, p->n_sys, p->sys_body_ptr.data(), tptr.data(), src_row.data(), uptr.data(),
-                            p->kind.data(), p->mu, 1, 2048, s));
+                            p->kind.data(), p->mu, 1,
+                            default_min_items(p->n_sys, p->sys_body_ptr.data(), tptr.data(), src_row.data(),
+                                              p->kind.data(), 0, kPlanMinItems),
+                            s));
     P2PLaunch L = fwd_launch(p, prec);
     L.trg_off = prec == MFS_MIXED ? d_o32.ptr : d_o64.ptr;
     L.trg_body = d_tb.as<int32_t>();
