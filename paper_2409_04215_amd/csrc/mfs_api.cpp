@@ -337,12 +337,21 @@ int standalone_operands(Workspace &ws, const Layout &lay, int kind, int64_t n_bo
     const size_t rec = kind == MFS_STOKES ? (prec == MFS_MIXED ? sizeof(SrcS32) : sizeof(SrcS64))
                                           : (prec == MFS_MIXED ? sizeof(SrcL32) : sizeof(SrcL64));
     MFS_TRY(grow(ws.src_ops, std::max<int64_t>(1, n_src) * rec));
-    MFS_TRY(launch_body_refpoint(n_body, lay.src_ptr.as<int32_t>(), lay.trg_ptr.as<int32_t>(), src_xyz, trg_xyz,
-                                 ws.centre.as<double>(), s));
-    MFS_TRY(launch_make_trg_off(n_trg, trg_xyz, lay.trg_body.as<int32_t>(), ws.centre.as<double>(), prec,
-                                ws.trg_off.ptr, s));
-    MFS_TRY(launch_make_src(n_src, kind, src_xyz, lay.src_body.as<int32_t>(), ws.centre.as<double>(), str, prec,
-                            ws.src_ops.ptr, s));
+    StandaloneOperands o;
+    o.n_body = n_body;
+    o.n_trg = n_trg;
+    o.n_src = n_src;
+    o.trg_ptr = lay.trg_ptr.as<int32_t>();
+    o.src_ptr = lay.src_ptr.as<int32_t>();
+    o.trg_body = lay.trg_body.as<int32_t>();
+    o.src_body = lay.src_body.as<int32_t>();
+    o.trg_xyz = trg_xyz;
+    o.src_xyz = src_xyz;
+    o.str = str;
+    o.centre = ws.centre.as<double>();
+    o.trg_off = ws.trg_off.ptr;
+    o.src_ops = ws.src_ops.ptr;
+    MFS_TRY(launch_operands(o, kind, prec, s));
     L.prec = prec;
     L.centre = ws.centre.as<double>();
     L.trg_body = lay.trg_body.as<int32_t>();
@@ -1114,9 +1123,21 @@ int p2p_stokes_noalloc(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
     if (n_items) MFS_HIP_TRY(hipMemcpyAsync(d_items, h.sorted, n_items * sizeof(P2PItem), hipMemcpyHostToDevice, s));
     MFS_TRY(launch_fill_body_ids(nb, d_trg_ptr, d_trg_body, s));
     MFS_TRY(launch_fill_body_ids(nb, d_src_ptr, d_src_body, s));
-    MFS_TRY(launch_body_refpoint(nb, d_src_ptr, d_trg_ptr, src_xyz, trg_xyz, d_centre, s));
-    MFS_TRY(launch_make_trg_off(nt, trg_xyz, d_trg_body, d_centre, prec, d_trg_off, s));
-    MFS_TRY(launch_make_src(ns, MFS_STOKES, src_xyz, d_src_body, d_centre, str, prec, d_src_ops, s));
+    StandaloneOperands o;
+    o.n_body = nb;
+    o.n_trg = nt;
+    o.n_src = ns;
+    o.trg_ptr = d_trg_ptr;
+    o.src_ptr = d_src_ptr;
+    o.trg_body = d_trg_body;
+    o.src_body = d_src_body;
+    o.trg_xyz = trg_xyz;
+    o.src_xyz = src_xyz;
+    o.str = str;
+    o.centre = d_centre;
+    o.trg_off = d_trg_off;
+    o.src_ops = d_src_ops;
+    MFS_TRY(launch_operands(o, MFS_STOKES, prec, s));
     P2PItems it;
     it.items = d_items;
     it.n_items = (int)n_items;

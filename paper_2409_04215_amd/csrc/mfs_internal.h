@@ -155,13 +155,17 @@ P2PItems items_of(const P2PPlan &pp);
 int launch_p2p(const P2PItems &it, const P2PLaunch &L, hipStream_t s);
 inline int launch_p2p(const P2PPlan &pp, const P2PLaunch &L, hipStream_t s) { return launch_p2p(items_of(pp), L, s); }
 
-// Standalone conversion: FP64 world points to the split representation.
-int launch_body_refpoint(int64_t n_body, const int32_t *src_ptr, const int32_t *trg_ptr, const double *src_xyz,
-                         const double *trg_xyz, double *centre, hipStream_t s);
-int launch_make_trg_off(int64_t n_trg, const double *xyz, const int32_t *trg_body, const double *centre,
-                        int prec, void *out, hipStream_t s);
-int launch_make_src(int64_t n_src, int kind, const double *xyz, const int32_t *src_body, const double *centre,
-                    const double *str, int prec, void *out, hipStream_t s);
+// Operands of a standalone call from its FP64 world points (all device pointers; trg_ptr, src_ptr,
+// trg_body and src_body describe the structure): the bodies' reference points `centre`, the
+// targets' offsets from them and the source records with their strengths.
+struct StandaloneOperands {
+    int64_t n_body = 0, n_trg = 0, n_src = 0;
+    const int32_t *trg_ptr = nullptr, *src_ptr = nullptr, *trg_body = nullptr, *src_body = nullptr;
+    const double *trg_xyz = nullptr, *src_xyz = nullptr, *str = nullptr;
+    double *centre = nullptr;
+    void *trg_off = nullptr, *src_ops = nullptr;
+};
+int launch_operands(const StandaloneOperands &o, int kind, int prec, hipStream_t s);
 int launch_fill_body_ids(int64_t n_body, const int32_t *ptr, int32_t *ids, hipStream_t s);
 
 // Position gradients of the pair sums (p2p_backward.hip): lane vectors indexed like the

@@ -448,60 +448,56 @@ __global__ void reduce_split_kernel(int64_t n, const double *__restrict__ partia
     out[v] = s;
 }
 
-// Reference point of every body for the standalone sums: its first source
-// point (or first target point if it has no sources).
-__global__ void body_ref_kernel(int64_t n_body, const int32_t *__restrict__ src_ptr,
-                                const int32_t *__restrict__ trg_ptr, const double *__restrict__ src_xyz,
-                                const double *__restrict__ trg_xyz, double *__restrict__ centre) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= n_body) return;
-    const double *p = nullptr;
-    if (src_ptr[b + 1] > src_ptr[b]) p = src_xyz + 3 * (int64_t)src_ptr[b];
-    else if (trg_ptr[b + 1] > trg_ptr[b]) p = trg_xyz + 3 * (int64_t)trg_ptr[b];
-    for (int c = 0; c < 3; ++c) centre[3 * b + c] = p ? p[c] : 0.0;
-}
-
 __global__ void fill_ids_kernel(int64_t n_body, const int32_t *__restrict__ ptr, int32_t *__restrict__ ids) {
     const int64_t b = blockIdx.x;
     if (b >= n_body) return;
     for (int32_t i = ptr[b] + threadIdx.x; i < ptr[b + 1]; i += blockDim.x) ids[i] = (int32_t)b;
 }
 
-__global__ void make_trg_off_kernel(int64_t n, const double *__restrict__ xyz, const int32_t *__restrict__ body,
-                                    const double *__restrict__ centre, int prec, void *__restrict__ out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int b = body[i];
-    const double o0 = xyz[3 * i] - centre[3 * b], o1 = xyz[3 * i + 1] - centre[3 * b + 1],
-                 o2 = xyz[3 * i + 2] - centre[3 * b + 2];
-    if (prec == MFS_MIXED) reinterpret_cast<float4 *>(out)[i] = make_float4((float)o0, (float)o1, (float)o2, 0.f);
-    else reinterpret_cast<double4 *>(out)[i] = make_double4(o0, o1, o2, 0.0);
+// Operands of a standalone call in one launch: thread k makes target k's offset, then source
+// k - n_trg's record, then body k - n_trg - n_src's reference point (its first source point, or
+// its first target point if it has no sources), which every point of the body reads for itself.
+__device__ __forceinline__ const double *body_ref(const StandaloneOperands &o, int b) {
+    if (o.src_ptr[b + 1] > o.src_ptr[b]) return o.src_xyz + 3 * (int64_t)o.src_ptr[b];
+    if (o.trg_ptr[b + 1] > o.trg_ptr[b]) return o.trg_xyz + 3 * (int64_t)o.trg_ptr[b];
+    return nullptr;
 }
 
-__global__ void make_src_kernel(int64_t n, int kind, const double *__restrict__ xyz, const int32_t *__restrict__ body,
-                                const double *__restrict__ centre, const double *__restrict__ str, int prec,
-                                void *__restrict__ out) {
-    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= n) return;
-    const int b = body[j];
-    const double o0 = xyz[3 * j] - centre[3 * b], o1 = xyz[3 * j + 1] - centre[3 * b + 1],
-                 o2 = xyz[3 * j + 2] - centre[3 * b + 2];
-    if (kind == MFS_STOKES) {
-        const double s0 = str ? str[3 * j] : 0.0, s1 = str ? str[3 * j + 1] : 0.0, s2 = str ? str[3 * j + 2] : 0.0;
-        if (prec == MFS_MIXED) {
-            SrcS32 v;
-            v.pos = make_float4((float)o0, (float)o1, (float)o2, 0.f);
-            v.str = make_float4((float)s0, (float)s1, (float)s2, 0.f);
-            reinterpret_cast<SrcS32 *>(out)[j] = v;
-        } else {
-            SrcS64 v = {{o0, o1, o2, 0.0}, {s0, s1, s2, 0.0}};
-            reinterpret_cast<SrcS64 *>(out)[j] = v;
-        }
-    } else {
-        const double q = str ? str[j] : 0.0;
-        if (prec == MFS_MIXED) reinterpret_cast<float4 *>(out)[j] = make_float4((float)o0, (float)o1, (float)o2, (float)q);
-        else reinterpret_cast<SrcL64 *>(out)[j] = SrcL64{{o0, o1, o2, q}};
+template <bool MIXED, bool STOKES>
+__global__ __launch_bounds__(256) void operands_kernel(StandaloneOperands o) {
+    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < o.n_trg) {
+        const double *c = body_ref(o, o.trg_body[k]), *x = o.trg_xyz + 3 * k;
+        const double d0 = x[0] - c[0], d1 = x[1] - c[1], d2 = x[2] - c[2];
+        if constexpr (MIXED) reinterpret_cast<float4 *>(o.trg_off)[k] = make_float4((float)d0, (float)d1, (float)d2, 0.f);
+        else reinterpret_cast<double4 *>(o.trg_off)[k] = make_double4(d0, d1, d2, 0.0);
+        return;
     }
+    k -= o.n_trg;
+    if (k < o.n_src) {
+        const double *c = body_ref(o, o.src_body[k]), *y = o.src_xyz + 3 * k;
+        const double d0 = y[0] - c[0], d1 = y[1] - c[1], d2 = y[2] - c[2];
+        if constexpr (STOKES) {
+            const double *f = o.str + 3 * k;
+            if constexpr (MIXED)
+                reinterpret_cast<SrcS32 *>(o.src_ops)[k] =
+                    SrcS32{make_float4((float)d0, (float)d1, (float)d2, 0.f),
+                           make_float4((float)f[0], (float)f[1], (float)f[2], 0.f)};
+            else
+                reinterpret_cast<SrcS64 *>(o.src_ops)[k] = SrcS64{{d0, d1, d2, 0.0}, {f[0], f[1], f[2], 0.0}};
+        } else {
+            const double q = o.str[k];
+            if constexpr (MIXED)
+                reinterpret_cast<SrcL32 *>(o.src_ops)[k] = make_float4((float)d0, (float)d1, (float)d2, (float)q);
+            else
+                reinterpret_cast<SrcL64 *>(o.src_ops)[k] = SrcL64{{d0, d1, d2, q}};
+        }
+        return;
+    }
+    k -= o.n_src;
+    if (k >= o.n_body) return;
+    const double *c = body_ref(o, (int)k);
+    for (int e = 0; e < 3; ++e) o.centre[3 * k + e] = c ? c[e] : 0.0;
 }
 
 }  // namespace
@@ -569,15 +565,6 @@ int launch_p2p(const P2PItems &pp, const P2PLaunch &L, hipStream_t s) {
     return MFS_OK;
 }
 
-int launch_body_refpoint(int64_t n_body, const int32_t *src_ptr, const int32_t *trg_ptr, const double *src_xyz,
-                         const double *trg_xyz, double *centre, hipStream_t s) {
-    if (n_body == 0) return MFS_OK;
-    body_ref_kernel<<<(unsigned)((n_body + 127) / 128), 128, 0, s>>>(n_body, src_ptr, trg_ptr, src_xyz, trg_xyz,
-                                                                     centre);
-    MFS_HIP_TRY(hipGetLastError());
-    return MFS_OK;
-}
-
 int launch_fill_body_ids(int64_t n_body, const int32_t *ptr, int32_t *ids, hipStream_t s) {
     if (n_body == 0) return MFS_OK;
     fill_ids_kernel<<<(unsigned)n_body, 256, 0, s>>>(n_body, ptr, ids);
@@ -585,18 +572,17 @@ int launch_fill_body_ids(int64_t n_body, const int32_t *ptr, int32_t *ids, hipSt
     return MFS_OK;
 }
 
-int launch_make_trg_off(int64_t n, const double *xyz, const int32_t *body, const double *centre, int prec,
-                        void *out, hipStream_t s) {
+int launch_operands(const StandaloneOperands &o, int kind, int prec, hipStream_t s) {
+    const int64_t n = o.n_trg + o.n_src + o.n_body;
     if (n == 0) return MFS_OK;
-    make_trg_off_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, xyz, body, centre, prec, out);
-    MFS_HIP_TRY(hipGetLastError());
-    return MFS_OK;
-}
-
-int launch_make_src(int64_t n, int kind, const double *xyz, const int32_t *body, const double *centre,
-                    const double *str, int prec, void *out, hipStream_t s) {
-    if (n == 0) return MFS_OK;
-    make_src_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, kind, xyz, body, centre, str, prec, out);
+    const unsigned grid = (unsigned)((n + 255) / 256);
+    if (prec == MFS_MIXED) {
+        if (kind == MFS_STOKES) operands_kernel<true, true><<<grid, 256, 0, s>>>(o);
+        else operands_kernel<true, false><<<grid, 256, 0, s>>>(o);
+    } else {
+        if (kind == MFS_STOKES) operands_kernel<false, true><<<grid, 256, 0, s>>>(o);
+        else operands_kernel<false, false><<<grid, 256, 0, s>>>(o);
+    }
     MFS_HIP_TRY(hipGetLastError());
     return MFS_OK;
 }
