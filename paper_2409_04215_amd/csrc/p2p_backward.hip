@@ -27,7 +27,7 @@ namespace {
 
 constexpr int BLOCK = 256;
 constexpr int WAVES = BLOCK / 64;
-constexpr int FLUSH = 64;
+constexpr int FLUSH = 32;  // three FP32 sums and the coefficient of w per run: shorter runs than the velocity sums
 
 struct GradArgs {
     const P2PItem *items;
