@@ -60,20 +60,26 @@ static int upload_vec(DevBuf &b, const std::vector<T> &v, hipStream_t s) {
 // ---------------------------------------------------------------------------
 // pair-sum work items
 // ---------------------------------------------------------------------------
+// Targets of one item: 64 lanes x tpl, the waves sharing the sources; 64 per wave for the Laplace
+// items of a launch with far tiles (laplace_far_item).
+int64_t item_targets(int kind, int tpl, bool far) { return far && kind == MFS_LAPLACE ? 256 : 64 * tpl; }
+
 // Shape of a pair-sum launch: bodies per source chunk (the largest chunk, so the
 // fewest split slices, that still gives at least min_items items), the number of
 // split slices and the number of items.
-void p2p_item_count(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr, int tpl,
-                    int min_items, int64_t *chunk_out, int *n_split_out, int64_t *n_items_out) {
-    const int blk = 64 * tpl;  // targets per item: 64 lanes x tpl (the pair kernels' item shape)
+void p2p_item_count(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
+                    const int32_t *kind_of_body, int kind_all, int tpl, bool far, int min_items, int64_t *chunk_out,
+                    int *n_split_out, int64_t *n_items_out) {
+    auto blocks = [&](int64_t sy) {  // target blocks of a system
+        const int64_t b0 = sys_body_ptr[sy], b1 = sys_body_ptr[sy + 1];
+        if (b1 == b0) return int64_t(0);
+        const int64_t blk = item_targets(kind_of_body ? kind_of_body[b0] : kind_all, tpl, far);
+        return (body_trg_ptr[b1] - body_trg_ptr[b0] + blk - 1) / blk;
+    };
     auto count_items = [&](int64_t chunk) {
         int64_t n = 0;
-        for (int64_t sy = 0; sy < n_sys; ++sy) {
-            const int64_t b0 = sys_body_ptr[sy], b1 = sys_body_ptr[sy + 1];
-            const int64_t nt = body_trg_ptr[b1] - body_trg_ptr[b0];
-            if (nt == 0 || b1 == b0) continue;
-            n += ((nt + blk - 1) / blk) * ((b1 - b0 + chunk - 1) / chunk);
-        }
+        for (int64_t sy = 0; sy < n_sys; ++sy)
+            n += blocks(sy) * ((sys_body_ptr[sy + 1] - sys_body_ptr[sy] + chunk - 1) / chunk);
         return n;
     };
     int64_t max_bodies = 1;
@@ -85,12 +91,7 @@ void p2p_item_count(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *b
         n_split = std::max(n_split, (int)((sys_body_ptr[sy + 1] - sys_body_ptr[sy] + chunk - 1) / chunk));
     // every system writes all n_split slices
     int64_t n = 0;
-    for (int64_t sy = 0; sy < n_sys; ++sy) {
-        const int64_t b0 = sys_body_ptr[sy], b1 = sys_body_ptr[sy + 1];
-        if (b1 == b0) continue;
-        const int64_t nt = body_trg_ptr[b1] - body_trg_ptr[b0];
-        n += ((nt + blk - 1) / blk) * n_split;
-    }
+    for (int64_t sy = 0; sy < n_sys; ++sy) n += blocks(sy) * n_split;
     *chunk_out = chunk;
     *n_split_out = n_split;
     *n_items_out = n;
@@ -99,11 +100,12 @@ void p2p_item_count(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *b
 int generate_p2p_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                        const int64_t *body_src_ptr, const int64_t *out_ptr, int out_dim,
                        const int32_t *kind_of_body, int kind_all, double mu, int tpl, int min_items, P2PItem *items,
-                       double *work, int32_t *order, P2PItem *sorted, int64_t cap, int64_t *n_items, int *n_split_out) {
-    const int blk = 64 * tpl;
+                       double *work, int32_t *order, P2PItem *sorted, int64_t cap, int64_t *n_items, int *n_split_out,
+                       bool far) {
     int64_t chunk = 1, n = 0;
     int n_split = 1;
-    p2p_item_count(n_sys, sys_body_ptr, body_trg_ptr, tpl, min_items, &chunk, &n_split, &n);
+    p2p_item_count(n_sys, sys_body_ptr, body_trg_ptr, kind_of_body, kind_all, tpl, far, min_items, &chunk, &n_split,
+                   &n);
 
     if (n > cap) return fail(MFS_EINVAL, "pair sum needs " + std::to_string(n) + " work items, more than " +
                                              std::to_string(cap));
@@ -115,6 +117,7 @@ int generate_p2p_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
         const int kind = kind_of_body ? kind_of_body[b0] : kind_all;
         const double scale = kind == MFS_STOKES ? 1.0 / (8.0 * PI * mu) : 1.0 / (4.0 * PI);
         const int dim = kind == MFS_STOKES ? 3 : 1;
+        const int64_t blk = item_targets(kind, tpl, far);
         const int64_t base = out_ptr ? out_ptr[b0] : (int64_t)out_dim * body_trg_ptr[b0];
         for (int64_t t0 = T0; t0 < T1; t0 += blk) {
             const int64_t t1 = std::min(t0 + blk, T1);
@@ -171,13 +174,44 @@ int default_min_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t 
     return (int)std::min((double)most, std::max(2048.0, 2048.0 * std::sqrt(us / 16.0)));
 }
 
+// Whether the sums of this orientation use far tiles: Laplace bodies only (beside them the Stokes
+// items of a launch would run with the far walk's registers, 4 waves per SIMD: 585 us instead of
+// 532 for a batch of both), a system of at least
+// 32 bodies (below, most are near some of an item's targets) and 2.5e8 pairs (below, 256 targets
+// to an item leave the chip too few: 48 bodies of 200 x 400 took 66 us instead of 60, 32 of
+// 389 x 777 79 us instead of 86), whole tiles but for a quarter, and bodies that are one FP32 run.
+bool use_far_tiles(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
+                   const int64_t *body_src_ptr, const int32_t *kind_of_body, std::vector<int32_t> &tile_ptr) {
+    int64_t most = 0, sources = 0, tiles = 0;
+    double pairs = 0.0;
+    tile_ptr.assign(std::max<int64_t>(1, sys_body_ptr[n_sys]), 0);
+    for (int64_t sy = 0; sy < n_sys; ++sy) {
+        const int64_t b0 = sys_body_ptr[sy], b1 = sys_body_ptr[sy + 1];
+        if (b1 == b0) continue;
+        if (kind_of_body && kind_of_body[b0] != MFS_LAPLACE) return false;
+        most = std::max(most, b1 - b0);
+        pairs += (double)(body_trg_ptr[b1] - body_trg_ptr[b0]) * (double)(body_src_ptr[b1] - body_src_ptr[b0]);
+        for (int64_t b = b0; b < b1; ++b) {
+            const int64_t n = body_src_ptr[b + 1] - body_src_ptr[b];
+            if (n > 1024) return false;  // FLUSH tiles, one FP32 run
+            tile_ptr[b] = (int32_t)tiles;
+            sources += n;
+            tiles += (n + 15) / 16;
+            if (tiles > INT32_MAX / 2) return false;
+        }
+    }
+    tile_ptr.push_back((int32_t)tiles);  // the total
+    return most >= 32 && pairs >= 2.5e8 && 16.0 * (double)tiles <= 1.25 * (double)sources;
+}
+
 int build_p2p_items(P2PPlan &pp, int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                     const int64_t *body_src_ptr, const int64_t *out_ptr, const int32_t *kind_of_body, double mu,
-                    int tpl, int min_items, hipStream_t s) {
+                    int tpl, int min_items, hipStream_t s, bool far) {
     pp.tpl = tpl;
+    pp.far = far;
     int64_t chunk = 1, cap = 0;
     int n_split = 1;
-    p2p_item_count(n_sys, sys_body_ptr, body_trg_ptr, tpl, min_items, &chunk, &n_split, &cap);
+    p2p_item_count(n_sys, sys_body_ptr, body_trg_ptr, kind_of_body, 0, tpl, far, min_items, &chunk, &n_split, &cap);
     std::vector<P2PItem> tmp(std::max<int64_t>(1, cap));
     std::vector<double> work(std::max<int64_t>(1, cap));
     std::vector<int32_t> order(std::max<int64_t>(1, cap));
@@ -185,7 +219,7 @@ int build_p2p_items(P2PPlan &pp, int64_t n_sys, const int64_t *sys_body_ptr, con
     int64_t n = 0;
     MFS_TRY(generate_p2p_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, out_ptr, 1, kind_of_body, 0, mu, tpl,
                                min_items, tmp.data(), work.data(), order.data(), pp.items.data(), cap, &n,
-                               &pp.n_split));
+                               &pp.n_split, far));
     pp.items.resize(n);
     if (!pp.items.empty()) MFS_TRY(upload_vec(pp.d_items, pp.items, s));
     MFS_TRY(pp.d_counter.reserve(sizeof(int)));
@@ -208,9 +242,12 @@ struct Layout {
     int variant = 0;  // which entry point family and kernel (see layout())
     uint64_t mu_bits = 0;
     std::vector<int64_t> sys, trg, src;  // host copies of the structure arrays (the cache key)
-    std::vector<int32_t> trg32, src32;
+    std::vector<int32_t> trg32, src32, tiles_h;
     DevBuf trg_ptr, src_ptr, trg_body, src_body;
     P2PPlan pp;
+    bool far_ok = false, far = false;  // far tiles: allowed, used
+    int64_t n_tiles = 0;
+    DevBuf tile_ptr;
     uint64_t last_use = 0;
 };
 
@@ -221,7 +258,7 @@ constexpr int kStandaloneMinItems = 16384;
 constexpr int kPlanMinItems = 65536;
 
 struct Workspace {
-    DevBuf centre, trg_off, src_ops, partial;
+    DevBuf centre, trg_off, src_ops, partial, far_tiles, far_centre, far_rho;
     std::vector<std::unique_ptr<Layout>> layouts;
     uint64_t clock = 0;
 };
@@ -274,12 +311,14 @@ int check_prec(int prec) {
 
 // The cached layout of (variant, mu, structure), built if missing.  kind sets
 // the items' kernel and scale; dim the output values per target of the items.
+// far_ok: the launch can take far tiles.
 int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_sys, const int64_t *sys_body_ptr,
-           const int64_t *body_trg_ptr, const int64_t *body_src_ptr, int64_t nb, hipStream_t s, Layout **out) {
+           const int64_t *body_trg_ptr, const int64_t *body_src_ptr, int64_t nb, hipStream_t s, Layout **out,
+           bool far_ok = false) {
     uint64_t bits;
     std::memcpy(&bits, &mu, sizeof bits);
     auto same = [&](const Layout &l) {
-        return l.variant == variant && l.mu_bits == bits && (int64_t)l.sys.size() == n_sys + 1 &&
+        return l.variant == variant && l.far_ok == far_ok && l.mu_bits == bits && (int64_t)l.sys.size() == n_sys + 1 &&
                (int64_t)l.trg.size() == nb + 1 && (int64_t)l.src.size() == nb + 1 &&
                std::equal(l.sys.begin(), l.sys.end(), sys_body_ptr) &&
                std::equal(l.trg.begin(), l.trg.end(), body_trg_ptr) &&
@@ -302,6 +341,7 @@ int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_s
     }
     auto l = std::make_unique<Layout>();
     l->variant = variant;
+    l->far_ok = far_ok;
     l->mu_bits = bits;
     l->sys.assign(sys_body_ptr, sys_body_ptr + n_sys + 1);
     l->trg.assign(body_trg_ptr, body_trg_ptr + nb + 1);
@@ -319,8 +359,15 @@ int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_s
     std::vector<int32_t> kob(std::max<int64_t>(1, nb), kind);
     const int min_items = default_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, kind,
                                             kStandaloneMinItems);
+    std::vector<int32_t> tiles;
+    l->far = far_ok && use_far_tiles(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, tiles);
+    if (l->far) {
+        l->tiles_h.swap(tiles);
+        l->n_tiles = l->tiles_h.back();
+        MFS_TRY(upload_vec(l->tile_ptr, l->tiles_h, s));
+    }
     MFS_TRY(build_p2p_items(l->pp, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, out_ptr.data(), kob.data(), mu, 1,
-                            min_items, s));
+                            min_items, s, l->far));
     l->last_use = ++ws.clock;
     *out = l.get();
     ws.layouts.push_back(std::move(l));
@@ -352,6 +399,16 @@ int standalone_operands(Workspace &ws, const Layout &lay, int kind, int64_t n_bo
     o.trg_off = ws.trg_off.ptr;
     o.src_ops = ws.src_ops.ptr;
     MFS_TRY(launch_operands(o, kind, prec, s));
+    if (lay.far) {
+        MFS_TRY(grow(ws.far_tiles, std::max<int64_t>(1, lay.n_tiles) * 1024));
+        MFS_TRY(grow(ws.far_centre, std::max<int64_t>(1, n_body) * 3 * sizeof(double)));
+        MFS_TRY(grow(ws.far_rho, std::max<int64_t>(1, n_body) * sizeof(float)));
+        L.far.tiles = ws.far_tiles.ptr;
+        L.far.tile_ptr = lay.tile_ptr.as<int32_t>();
+        L.far.centre = ws.far_centre.as<double>();
+        L.far.rho = ws.far_rho.as<float>();
+        MFS_TRY(launch_far_pack(n_body, o.src_ptr, src_xyz, 3, nullptr, L.far, s));
+    }
     L.prec = prec;
     L.centre = ws.centre.as<double>();
     L.trg_body = lay.trg_body.as<int32_t>();
@@ -384,7 +441,8 @@ int p2p_standalone(int kind, int64_t n_sys, const int64_t *sys_body_ptr, const i
     Workspace &ws = workspace();
     const int dim = kind == MFS_STOKES ? 3 : 1;
     Layout *lay = nullptr;
-    MFS_TRY(layout(ws, kind, kind, dim, mu, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nb, s, &lay));
+    MFS_TRY(layout(ws, kind, kind, dim, mu, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nb, s, &lay,
+                   kind == MFS_LAPLACE && prec == MFS_MIXED));
     P2PLaunch L;
     MFS_TRY(standalone_operands(ws, *lay, kind, nb, nt, ns, trg_xyz, src_xyz, str, prec, s, L));
     L.skip_same = (flags & MFS_SKIP_SAME_BODY) != 0;
@@ -506,6 +564,22 @@ struct mfs_plan_s {
     DevBuf d_src_body, d_trg_body;
     // pair operands: forward (sources = proxies), transposed (sources = collocation points)
     DevBuf fS32, fL32, fS64, fL64, tS32, tL32, tS64, tL64;
+    // far tiles (mixed sums of Laplace plans), forward and transposed sources, and their work items
+    struct Far {
+        bool use = false;
+        P2PPlan items;
+        DevBuf tiles, tile_ptr, centre, rho;
+        FarTiles view() const {
+            FarTiles f;
+            if (use) {
+                f.tiles = tiles.ptr;
+                f.tile_ptr = tile_ptr.as<int32_t>();
+                f.centre = centre.as<double>();
+                f.rho = rho.as<float>();
+            }
+            return f;
+        }
+    } far_fwd, far_tr;
     // factors
     DevBuf A32, A64;
     std::vector<Factor> factors;
@@ -936,6 +1010,19 @@ int factor_shapes(mfs_plan p, const mfs_plan_desc *d, const std::vector<int64_t>
 
 }  // namespace
 
+// The work items of the far walks, in the shape of the plan's other pair sums.
+static int build_far_items(mfs_plan_s *p, int min_items, bool persistent, hipStream_t s) {
+    const std::vector<int64_t> &src_row = p->src_row, &trg_row = p->trg_row;
+    if (p->far_fwd.use)
+        MFS_TRY(build_p2p_items(p->far_fwd.items, p->n_sys, p->sys_body_ptr.data(), trg_row.data(), src_row.data(),
+                                p->gam_off.data(), p->kind.data(), p->mu, 1, min_items, s, true));
+    if (p->far_tr.use)
+        MFS_TRY(build_p2p_items(p->far_tr.items, p->n_sys, p->sys_body_ptr.data(), src_row.data(), trg_row.data(),
+                                p->lam_off.data(), p->kind.data(), p->mu, 1, min_items, s, true));
+    p->far_fwd.items.persistent = p->far_tr.items.persistent = persistent;
+    return MFS_OK;
+}
+
 // Everything of a plan that depends on where the bodies are: centres, rotations,
 // world-axis offsets of every point (FP64 and FP32), per-body Gram inverses
 // G^-1 = R G0^-1 R^T, and the positions in the pair-operand records (strengths
@@ -1007,6 +1094,12 @@ static int upload_geometry(mfs_plan_s *p, const double *centre, const double *ro
     };
     MFS_TRY(records(p->n_srcp, so64, so32, p->fS32, p->fL32, p->fS64, p->fL64));
     MFS_TRY(records(p->n_trgp, to64, to32, p->tS32, p->tL32, p->tS64, p->tL64));
+    if (p->far_fwd.use)
+        MFS_TRY(launch_far_pack(nb, p->d_src_row32.as<int32_t>(), p->d_src_off64.as<double>(), 4,
+                                p->d_centre.as<double>(), p->far_fwd.view(), s));
+    if (p->far_tr.use)
+        MFS_TRY(launch_far_pack(nb, p->d_trg_row32.as<int32_t>(), p->d_trg_off64.as<double>(), 4,
+                                p->d_centre.as<double>(), p->far_tr.view(), s));
     return MFS_OK;
 }
 
@@ -1351,6 +1444,21 @@ int mfs_plan_create(mfs_plan *out, const mfs_plan_desc *d, void *stream) {
     MFS_TRY(upload_vec(p->d_trg_row32, trg_row32, s));
     MFS_TRY(upload_vec(p->d_src_body, sbody, s));
     MFS_TRY(upload_vec(p->d_trg_body, tbody, s));
+    auto far_buffers = [&](mfs_plan_s::Far &f, const std::vector<int64_t> &trg, const std::vector<int64_t> &src) -> int {
+        std::vector<int32_t> tiles;
+        if (p->prec != MFS_MIXED ||
+            !use_far_tiles(p->n_sys, p->sys_body_ptr.data(), trg.data(), src.data(), p->kind.data(), tiles))
+            return MFS_OK;
+        MFS_TRY(f.tiles.reserve((size_t)tiles.back() * 1024));
+        MFS_TRY(f.centre.reserve(nb * 3 * sizeof(double)));
+        MFS_TRY(f.rho.reserve(nb * sizeof(float)));
+        MFS_TRY(upload_vec(f.tile_ptr, tiles, s));
+        MFS_HIP_TRY(hipStreamSynchronize(s));  // `tiles` is pageable and local
+        f.use = true;
+        return MFS_OK;
+    };
+    MFS_TRY(far_buffers(p->far_fwd, p->trg_row, p->src_row));
+    MFS_TRY(far_buffers(p->far_tr, p->src_row, p->trg_row));
     MFS_TRY(upload_geometry(p.get(), d->centre, d->rot, s));
     // pair-sum items, forward (targets = collocation points) and transposed (targets = proxies)
     {
@@ -1366,6 +1474,7 @@ int mfs_plan_create(mfs_plan *out, const mfs_plan_desc *d, void *stream) {
                                 p->gam_off.data(), p->kind.data(), p->mu, 1, min_items, s));
         MFS_TRY(build_p2p_items(p->p2p_tr1, p->n_sys, p->sys_body_ptr.data(), src_row.data(), trg_row.data(),
                                 p->lam_off.data(), p->kind.data(), p->mu, 1, min_items, s));
+        MFS_TRY(build_far_items(p.get(), min_items, false, s));
     }
     // workspace
     {
@@ -1377,7 +1486,8 @@ int mfs_plan_create(mfs_plan *out, const mfs_plan_desc *d, void *stream) {
         MFS_TRY(p->ws_l64a.reserve(nl * sizeof(double)));
         MFS_TRY(p->ws_l64b.reserve(nl * sizeof(double)));
         MFS_TRY(p->ws_l64c.reserve(nl * sizeof(double)));
-        const int ns = std::max({p->p2p_fwd.n_split, p->p2p_tr.n_split, p->p2p_fwd1.n_split, p->p2p_tr1.n_split});
+        const int ns = std::max({p->p2p_fwd.n_split, p->p2p_tr.n_split, p->p2p_fwd1.n_split, p->p2p_tr1.n_split,
+                                 p->far_fwd.items.n_split, p->far_tr.items.n_split});
         const int64_t nv = std::max({ng, nl, 3 * p->n_srcp, 3 * p->n_trgp});
         MFS_TRY(p->partial.reserve((size_t)(ns > 1 ? ns : 1) * nv * sizeof(double)));
         MFS_TRY(p->sys_active.reserve(p->n_sys * sizeof(int32_t)));
@@ -1522,6 +1632,14 @@ int precond_tr(mfs_plan p, const double *in, int prec, bool project, double *out
     return launch_rotate_out(bv, p->ws_g64.ptr, false, out, false, s);
 }
 
+// The work items of a plan's pair sums
+const P2PPlan &fwd_items(mfs_plan p, int prec) {
+    return prec == MFS_MIXED && p->far_fwd.use && p->p2p_fwd.tpl == 1 ? p->far_fwd.items : p->p2p_fwd;
+}
+const P2PPlan &tr_items(mfs_plan p, int prec) {
+    return prec == MFS_MIXED && p->far_tr.use && p->p2p_tr.tpl == 1 ? p->far_tr.items : p->p2p_tr;
+}
+
 P2PLaunch fwd_launch(mfs_plan p, int prec) {
     P2PLaunch L;
     L.prec = prec;
@@ -1531,6 +1649,7 @@ P2PLaunch fwd_launch(mfs_plan p, int prec) {
     L.trg_off = prec == MFS_MIXED ? p->d_trg_off32.ptr : p->d_trg_off64.ptr;
     L.srcS = prec == MFS_MIXED ? p->fS32.ptr : p->fS64.ptr;
     L.srcL = prec == MFS_MIXED ? p->fL32.ptr : p->fL64.ptr;
+    L.far = p->far_fwd.view();
     L.partial = p->partial.as<double>();
     L.n_val = p->n_gamma;
     return L;
@@ -1545,6 +1664,7 @@ P2PLaunch tr_launch(mfs_plan p, int prec) {
     L.trg_off = prec == MFS_MIXED ? p->d_src_off32.ptr : p->d_src_off64.ptr;
     L.srcS = prec == MFS_MIXED ? p->tS32.ptr : p->tS64.ptr;
     L.srcL = prec == MFS_MIXED ? p->tL32.ptr : p->tL64.ptr;
+    L.far = p->far_tr.view();
     L.partial = p->partial.as<double>();
     L.n_val = p->n_lambda;
     return L;
@@ -1599,7 +1719,7 @@ int matvec_impl(mfs_plan p, const double *gamma, double *out, int prec, const in
         L.ev_stop = t.ev[2 * t.used + 1];
         ++t.used;
     }
-    return launch_p2p(p->p2p_fwd, L, s);
+    return launch_p2p(fwd_items(p, prec), L, s);
 }
 
 // (A^T w)^(k') = w^(k') + R (S_L^+)^T R^T (I - L^(k')) sum_{k != k'} S^(kk')T w^(k)
@@ -1609,7 +1729,7 @@ int matvec_adjoint_impl(mfs_plan p, const double *w, double *out, int prec, cons
     L.skip_same = true;
     L.out = p->ws_l64c.as<double>();
     L.sys_active = sys_active;
-    MFS_TRY(launch_p2p(p->p2p_tr, L, s));
+    MFS_TRY(launch_p2p(tr_items(p, prec), L, s));
     if (p->formulation == MFS_MOBILITY)
         MFS_TRY(launch_project(p->view(), p->ws_l64c.as<double>(), false, false, true, p->ws_l64c.as<double>(),
                                nullptr, nullptr, 0, s));
@@ -1640,7 +1760,7 @@ int mfs_rhs(mfs_plan p, const double *net, double *b, double *strength0, int pre
     Lr.skip_same = false;
     Lr.alpha = -1.0;
     Lr.out = b;
-    return launch_p2p(p->p2p_fwd, Lr, s);
+    return launch_p2p(fwd_items(p, prec), Lr, s);
 }
 
 int mfs_precond_apply(mfs_plan p, const double *in, double *out, int flags, int prec, void *stream) {
@@ -2100,7 +2220,7 @@ extern "C" int mfs_gmres_solve_backward(mfs_plan p, const double *gamma, const d
         Ln.skip_same = false;
         Ln.alpha = -1.0;
         Ln.out = p->ws_l64c.as<double>();
-        MFS_TRY(launch_p2p(p->p2p_tr, Ln, s));
+        MFS_TRY(launch_p2p(tr_items(p, prec), Ln, s));
         MFS_TRY(launch_grad_net(bv, p->ws_l64c.as<double>(), grad_net, s));
     }
     MFS_HIP_TRY(hipStreamSynchronize(s));
@@ -2188,7 +2308,8 @@ extern "C" int mfs_plan_autotune(mfs_plan p, int32_t prec, int32_t reps, int32_t
             for (int mi : mis) {
                 P2PPlan cand;
                 status = build_p2p_items(cand, p->n_sys, p->sys_body_ptr.data(), trg_row.data(), src_row.data(),
-                                         p->gam_off.data(), p->kind.data(), p->mu, tpl, mi, s);
+                                         p->gam_off.data(), p->kind.data(), p->mu, tpl, mi, s,
+                                         prec == MFS_MIXED && p->far_fwd.use && tpl == 1);
                 if (status < 0) break;
                 cand.persistent = per != 0;
                 const int64_t need = (cand.n_split > 1 ? cand.n_split : 1) * std::max<int64_t>(1, p->n_gamma);
@@ -2234,11 +2355,14 @@ extern "C" int mfs_plan_autotune(mfs_plan p, int32_t prec, int32_t reps, int32_t
                             p->gam_off.data(), p->kind.data(), p->mu, btpl, bmi, s));
     MFS_TRY(build_p2p_items(p->p2p_tr, p->n_sys, p->sys_body_ptr.data(), src_row.data(), trg_row.data(),
                             p->lam_off.data(), p->kind.data(), p->mu, btpl, bmi, s));
+    MFS_TRY(build_far_items(p, bmi, bper, s));
     p->p2p_fwd.persistent = p->p2p_tr.persistent = bper;
     p->tuned_persistent = bper;
     MFS_HIP_TRY(hipStreamSynchronize(s));
-    MFS_TRY(grow_partial(p, (int64_t)std::max(p->p2p_fwd.n_split, 1) * std::max<int64_t>(1, p->n_gamma)));
-    MFS_TRY(grow_partial(p, (int64_t)std::max(p->p2p_tr.n_split, 1) * std::max<int64_t>(1, p->n_lambda)));
+    MFS_TRY(grow_partial(p, (int64_t)std::max({p->p2p_fwd.n_split, p->far_fwd.items.n_split, 1}) *
+                                std::max<int64_t>(1, p->n_gamma)));
+    MFS_TRY(grow_partial(p, (int64_t)std::max({p->p2p_tr.n_split, p->far_tr.items.n_split, 1}) *
+                                std::max<int64_t>(1, p->n_lambda)));
     // captured graphs hold the old work tables and buffers
     for (auto &row : p->graph)
         for (auto &g : row)
@@ -2275,9 +2399,12 @@ extern "C" int mfs_plan_set_launch(mfs_plan p, int32_t targets_per_lane, int32_t
                             p->gam_off.data(), p->kind.data(), p->mu, targets_per_lane, work_items, s));
     MFS_TRY(build_p2p_items(p->p2p_tr, p->n_sys, p->sys_body_ptr.data(), src_row.data(), trg_row.data(),
                             p->lam_off.data(), p->kind.data(), p->mu, targets_per_lane, work_items, s));
+    MFS_TRY(build_far_items(p, work_items, persistent != 0, s));
     p->p2p_fwd.persistent = p->p2p_tr.persistent = persistent != 0;
-    MFS_TRY(grow_partial(p, (int64_t)std::max(p->p2p_fwd.n_split, 1) * std::max<int64_t>(1, p->n_gamma)));
-    MFS_TRY(grow_partial(p, (int64_t)std::max(p->p2p_tr.n_split, 1) * std::max<int64_t>(1, p->n_lambda)));
+    MFS_TRY(grow_partial(p, (int64_t)std::max({p->p2p_fwd.n_split, p->far_fwd.items.n_split, 1}) *
+                                std::max<int64_t>(1, p->n_gamma)));
+    MFS_TRY(grow_partial(p, (int64_t)std::max({p->p2p_tr.n_split, p->far_tr.items.n_split, 1}) *
+                                std::max<int64_t>(1, p->n_lambda)));
     for (auto &row : p->graph)
         for (auto &g : row)
             if (g) {
@@ -2356,7 +2483,7 @@ extern "C" int mfs_surface_residual(mfs_plan p, const double *sigma, const doubl
                             p->kind.data(), p->mu, 1,
                             default_min_items(p->n_sys, p->sys_body_ptr.data(), tptr.data(), src_row.data(),
                                               p->kind.data(), 0, kPlanMinItems),
-                            s));
+                            s, p->far_fwd.use && prec == MFS_MIXED));
     P2PLaunch L = fwd_launch(p, prec);
     L.trg_off = prec == MFS_MIXED ? d_o32.ptr : d_o64.ptr;
     L.trg_body = d_tb.as<int32_t>();

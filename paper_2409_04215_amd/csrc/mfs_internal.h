@@ -91,6 +91,16 @@ struct P2PItem {
     int32_t pad;
 };
 
+// Matrix-core operands of the Laplace sources of one orientation (mixed precision): 64 x 16 bytes
+// per 16 sources of a body, the body's first tile, the mean of its sources and their largest distance
+// from it.  tiles null: not used.
+struct FarTiles {
+    void *tiles = nullptr;
+    const int32_t *tile_ptr = nullptr;  // [n_body]
+    double *centre = nullptr;           // [n_body][3]
+    float *rho = nullptr;               // [n_body]
+};
+
 // Everything one pair-sum launch reads and writes (device pointers).
 struct P2PLaunch {
     int prec = MFS_MIXED;
@@ -104,6 +114,7 @@ struct P2PLaunch {
     const void *trg_off = nullptr;        // float4 / double4 [n_trg] offsets from the body centre
     const void *srcS = nullptr;           // SrcS32 / SrcS64 [n_src] (Stokes bodies)
     const void *srcL = nullptr;           // SrcL32 / SrcL64 [n_src] (Laplace bodies)
+    FarTiles far;                         // mixed Laplace sums of one target per lane
     double *out = nullptr;                // final output [n_val]
     double *partial = nullptr;            // [n_split][n_val] when n_split > 1
     const double *addend = nullptr;       // added once to the output (may be null)
@@ -117,6 +128,7 @@ struct P2PPlan {
     std::vector<P2PItem> items;
     int n_split = 1;
     int tpl = 1;
+    bool far = false;            // Laplace items of 256 targets for the far walk (tpl 1)
     bool persistent = false;     // fixed grid + work-queue counter instead of one workgroup per item
     int persistent_grid = 2048;  // workgroups of a persistent launch
     DevBuf d_items;
@@ -124,10 +136,11 @@ struct P2PPlan {
 };
 
 // items for targets grouped by body (body_trg_ptr), bodies grouped by system;
-// out_ptr[b] = output offset of body b's first target; dim_of_body 1 or 3.
+// out_ptr[b] = output offset of body b's first target; dim_of_body 1 or 3.  far: for launches with
+// far tiles (one target per lane).
 int build_p2p_items(P2PPlan &pp, int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                     const int64_t *body_src_ptr, const int64_t *out_ptr, const int32_t *kind_of_body,
-                    double mu, int tpl, int min_items, hipStream_t s);
+                    double mu, int tpl, int min_items, hipStream_t s, bool far = false);
 
 // The same items written into caller-provided host arrays, with no heap
 // allocation: out_ptr may be null (then out_dim * body_trg_ptr[b]) and
@@ -137,7 +150,8 @@ int build_p2p_items(P2PPlan &pp, int64_t n_sys, const int64_t *sys_body_ptr, con
 int generate_p2p_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                        const int64_t *body_src_ptr, const int64_t *out_ptr, int out_dim,
                        const int32_t *kind_of_body, int kind, double mu, int tpl, int min_items, P2PItem *items,
-                       double *work, int32_t *order, P2PItem *sorted, int64_t cap, int64_t *n_items, int *n_split);
+                       double *work, int32_t *order, P2PItem *sorted, int64_t cap, int64_t *n_items, int *n_split,
+                       bool far = false);
 
 // A pair-sum launch's items wherever they live (device pointers).
 struct P2PItems {
@@ -145,6 +159,7 @@ struct P2PItems {
     int n_items = 0;
     int n_split = 1;
     int tpl = 1;
+    bool far = false;
     bool persistent = false;
     int persistent_grid = 2048;
     int *counter = nullptr;  // persistent mode only
@@ -166,6 +181,10 @@ struct StandaloneOperands {
     void *trg_off = nullptr, *src_ops = nullptr;
 };
 int launch_operands(const StandaloneOperands &o, int kind, int prec, hipStream_t s);
+// Far tiles of Laplace bodies: sources of body b at rows ptr[b].. of pos [n][stride], from base
+// [n_body][3] (null: the origin).
+int launch_far_pack(int64_t n_body, const int32_t *ptr, const double *pos, int stride, const double *base,
+                    const FarTiles &far, hipStream_t s);
 int launch_fill_body_ids(int64_t n_body, const int32_t *ptr, int32_t *ids, hipStream_t s);
 
 // Position gradients of the pair sums (p2p_backward.hip): lane vectors indexed like the

@@ -27,6 +27,10 @@
 //    with |d| plus the body size.  Per pair: FP32 arithmetic with the hardware
 //    v_rsq_f32; per run of at most FLUSH sources the FP32 partial is added
 //    to an FP64 accumulator.
+//  * Laplace sources far from all the item's targets go through the matrix cores
+//    (far_body): |x - y|^2 = |x|^2 - 2 x.y + |y|^2 is one v_mfma_f32_16x16x32_bf16
+//    per 16 targets x 16 sources, from exact three-way splits of FP32 coordinates,
+//    which leaves a pair v_rsq_f32 and one FMA of its 8 VALU instructions.
 //  * FP64 variant: the same walk in FP64, 1/sqrt from v_rsq_f64 refined by
 //    one third-order step (rsqrt_f64 in device_math.h).
 //  * Same-body pairs: a source body equal to every active lane's own body is
@@ -126,12 +130,23 @@ __device__ __forceinline__ void laplace_pairs(const float (&xr)[TPL][3], const f
         for (int t = 0; t < TPL; ++t) p[t] = __builtin_fmaf(q[u], ri[u][t], p[t]);
 }
 
+// Orders a wave's LDS stores before its later reads of them (its accesses complete in order).
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // This wave's contiguous quarter [j0, j1) of the source range [b0, b1).
 __device__ __forceinline__ void wave_range(int b0, int b1, int wv, int &j0, int &j1) {
     const int q = (b1 - b0 + WAVES - 1) / WAVES;
     j0 = min(b0 + wv * q, b1);
     j1 = min(j0 + q, b1);
 }
+
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
 
 struct KernelArgs {
     const P2PItem *items;
@@ -147,7 +162,174 @@ struct KernelArgs {
     int accumulate;
     int *queue;                // persistent mode: work-queue counter (reset to 0 before the launch), else null
     int n_items;
+    const uint4v *far_tiles;      // Laplace far tiles (pack_far_tile), 64 per tile
+    const int32_t *far_tile_ptr;  // [n_body] first tile of a body
+    const double *far_centre;     // [n_body][3] the point a body's tiles are relative to
+    const float *far_rho;         // [n_body] largest distance of a source from it
 };
+
+// ---------------------------------------------------------------------------
+// Laplace sources far from a block of targets
+//
+// The 32 k slots of the bf16 MFMA hold, for a target x and a source y relative to the mean of
+// the body's sources, group by group of eight (lane l holds group l/16):
+//   0..2:  coordinate c of x and of -2 y as three bf16 pieces a + m + l, which is FP32 exactly;
+//          eight of the nine products of pieces (l l is below 2^-32 of x.y)
+//   3:     |x|^2 in four pieces against ones, ones against |y|^2 in four pieces
+// with |x|^2 and |y|^2 from the FP64 coordinates.  Products of pieces are exact in FP32 and the
+// matrix core adds the slots with a rounding of 0.28 ulp of the largest (measured, rms), so for
+// |x| >= 2 |y| r^2 errs by less than the subtracted coordinates' does (0.33e-7 |x|^2, where
+// rounding x alone leaves 0.7e-7 |x| r).  Bodies nearer than that, bodies with a target of their
+// own in the block and extreme scales take the VALU path.
+// Rate: a pair is v_rsq_f32 and one FMA on the VALU (5.2 ns per 64 pairs and SIMD in a bare
+// loop, 13.3 with the six operations of r^2), the MFMA (1.7 ns) runs beside them.
+// 250 bodies, 389 sources and 777 targets each: 3285 -> 2354 us (8.0e12 pairs/s).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ float bf16_head(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {  // both exact in bf16
+    return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+__device__ __forceinline__ void split3(float x, float &a, float &m, float &l) {
+    a = bf16_head(x);
+    const float r = x - a;
+    m = bf16_head(r);
+    l = r - m;
+}
+__device__ __forceinline__ void split4(double x, float (&p)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        p[i] = bf16_head((float)x);
+        x -= p[i];
+    }
+}
+constexpr uint32_t BF16_ONES = 0x3f803f80u;
+
+// Column l%16 of tile k of nt is source nt (l%16) + k, so that a lane's sums run over
+// neighbouring sources: oscillating strengths cancel early there as in the VALU runs (sources dealt
+// out 16 apart left up to twice their error).
+__device__ __forceinline__ int far_source(int k, int nt, int lane) { return nt * (lane & 15) + k; }
+// A lane's 16 bytes of a tile for its source's offset y from the body's centre.
+__device__ __forceinline__ uint4v pack_far_tile(const double (&y)[3], int lane) {
+    const int g = lane >> 4;
+    if (g < 3) {
+        float a, m, l;
+        split3(-2.0f * (float)y[g], a, m, l);
+        return uint4v{bf16_pair(a, m), bf16_pair(l, a), bf16_pair(m, l), bf16_pair(a, m)};
+    }
+    float p[4];
+    split4(y[0] * y[0] + y[1] * y[1] + y[2] * y[2], p);
+    return uint4v{BF16_ONES, BF16_ONES, bf16_pair(p[0], p[1]), bf16_pair(p[2], p[3])};
+}
+
+// Sums of one wave's far bodies.  run: targets 16 t + 4 (l/16) + r against the sources l%16 of the
+// tiles since the last flush; sum: the flushed total of target far_target(l).
+struct FarSums {
+    float run[16];
+    double sum;
+    int tiles;  // since the last flush
+};
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double x) {  // x of another lane of the row of 16
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+
+// Adds run into the totals: the 16 values are summed over the row's 16 lanes in FP64, every
+// exchange halving what a lane carries, which leaves lane l value i = l%16.
+__device__ __forceinline__ void far_flush(FarSums &fs) {
+    const int lane = threadIdx.x & 63;
+    double v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        v[i] = (double)fs.run[i];
+        fs.run[i] = 0.f;
+    }
+#pragma unroll
+    for (int h = 8; h >= 1; h >>= 1) {
+        const bool up = (lane & h) != 0;
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+            const double lo = v[i], hi = v[i + h];
+            const double send = up ? +lo : +hi, keep = up ? +hi : +lo;  // values: a choice of elements is indexing
+            double got;
+            if (h == 8) got = dpp_move<0x128>(send);       // row_ror:8
+            else if (h == 4) got = dpp_move<0x1B>(dpp_move<0x141>(send));  // row_half_mirror, quad_perm [3,2,1,0]
+            else if (h == 2) got = dpp_move<0x4E>(send);   // quad_perm [2,3,0,1]
+            else got = dpp_move<0xB1>(send);               // quad_perm [1,0,3,2]
+            v[i] = keep + got;
+        }
+    }
+    fs.sum += v[0];
+    fs.tiles = 0;
+}
+__device__ __forceinline__ int far_target(int lane) {  // value i = 4 t + r of row g: target 16 t + 4 g + r
+    return 16 * ((lane & 15) >> 2) + 4 * (lane >> 4) + (lane & 3);
+}
+
+// All sources of one far body against the wave's 64 targets; x: this lane's target relative to
+// the body's centre, frag: 4 KB and str: 1024 floats of the wave's own.  The next
+// tile is fetched while this one is summed (250 bodies of 389 sources: 2336 us, two ahead 2411,
+// four 2729: registers).  FAR_RUN tiles make a sum of their own first (a tenth off the error of a
+// sum over ill-conditioned strengths, for one FMA in FAR_RUN).
+constexpr int FAR_RUN = 8;
+__device__ __forceinline__ void far_body(const uint4v *__restrict__ tiles, const SrcL32 *__restrict__ src, int n,
+                                         const double (&x)[3], uint4v *frag, float *str, FarSums &fs) {
+    const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
+    const int nt = (n + 15) / 16;  // at most FLUSH
+    if (fs.tiles + nt > FLUSH) far_flush(fs);
+    fs.tiles += nt;
+    uint4v B = tiles[(unsigned)lane];
+    for (int j = lane; j < 16 * nt; j += 64) str[j] = j < n ? src[j].w : 0.f;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        float a, m, l;
+        split3((float)x[c], a, m, l);
+        frag[64 * c + lane] = uint4v{bf16_pair(a, a), bf16_pair(a, m), bf16_pair(m, m), bf16_pair(l, l)};
+    }
+    float p[4];
+    split4(x[0] * x[0] + x[1] * x[1] + x[2] * x[2], p);
+    frag[192 + lane] = uint4v{bf16_pair(p[0], p[1]), bf16_pair(p[2], p[3]), BF16_ONES, BF16_ONES};
+    wave_lds_order();
+    bf16x8 A[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) A[t] = __builtin_bit_cast(bf16x8, frag[64 * g + 16 * t + c16]);
+    __builtin_amdgcn_wave_barrier();  // the next body's stores follow these reads
+    for (int kr = 0; kr < nt; kr += FAR_RUN) {
+        const int kend = min(kr + FAR_RUN, nt);
+        float part[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) part[i] = 0.f;
+        for (int k = kr; k < kend; ++k) {
+            const bf16x8 Bk = __builtin_bit_cast(bf16x8, B);
+            const float q = str[far_source(k, nt, lane)];
+            B = (tiles + 64 * (int64_t)min(k + 1, nt - 1))[(unsigned)lane];  // uniform base, 32-bit lane offset
+            const float4v zero = {0.f, 0.f, 0.f, 0.f};
+            float4v r2[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) r2[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[t], Bk, zero, 0, 0, 0);
+            rsq_cluster_begin();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) r2[i / 4][i % 4] = __builtin_amdgcn_rsqf(r2[i / 4][i % 4]);
+            rsq_cluster_end();
+#pragma unroll
+            for (int i = 0; i < 16; ++i) part[i] = __builtin_fmaf(q, r2[i / 4][i % 4], part[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) fs.run[i] += part[i];
+    }
+}
+
+// The wave's far sums, lane l: target l
+__device__ __forceinline__ double far_total(FarSums &fs, uint4v *frag) {
+    far_flush(fs);
+    const int lane = threadIdx.x & 63;
+    double *tot = reinterpret_cast<double *>(frag);
+    tot[far_target(lane)] = fs.sum;
+    wave_lds_order();
+    return tot[lane];
+}
 
 // ---------------------------------------------------------------------------
 // Mixed precision, Stokes / Laplace (one kernel; item.kind is wave-uniform)
@@ -237,9 +419,7 @@ __device__ __forceinline__ void mixed_item(const KernelArgs &a, const P2PItem it
 #pragma unroll
                 for (int t = 0; t < TPL; ++t) p[t] = 0.f;
                 if (lane < cnt) slot[lane] = srcL[jb + lane];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                wave_lds_order();
                 int k = 0;
                 for (; k + 8 <= cnt; k += 8) laplace_pairs<TPL, 8>(xr, slot + k, p);
                 for (; k < cnt; ++k) laplace_pairs<TPL, 1>(xr, slot + k, p);
@@ -269,6 +449,70 @@ __device__ __forceinline__ void mixed_item(const KernelArgs &a, const P2PItem it
             out[o + c] = v;
         }
     }
+}
+
+// One Laplace item of a launch with far tiles: 64 targets per wave, so that the four waves read the
+// same tiles at about the same time (the tiles of 250 bodies, 6 MB, do not stay in an XCD's L2:
+// with one block of targets per item and the far bodies dealt to its waves a 250-body sum took
+// 1.08 times as long).
+__device__ __forceinline__ void laplace_far_item(const KernelArgs &a, const P2PItem it,
+                                                 const float4 *__restrict__ trg_off, const SrcL32 *__restrict__ srcL,
+                                                 float4 *stage, uint4v *frags, float *strs) {
+    const bool active = !a.sys_active || a.sys_active[it.sys];
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int t0 = it.t0 + 64 * wv;
+    if (t0 >= it.t1) return;
+    uint4v *frag = frags + 256 * wv;
+    float *str = strs + 1024 * wv;
+    float4 *slot = stage + 64 * wv;
+    const int idx = t0 + lane;
+    const bool valid = idx < it.t1;
+    const int i = valid ? idx : t0;  // lanes past the last target repeat the wave's first one
+    const int body = a.trg_body[i];
+    const float4 xt = trg_off[i];
+    const double ct0 = a.centre[3 * body], ct1 = a.centre[3 * body + 1], ct2 = a.centre[3 * body + 2];
+    double acc = 0.0;
+    FarSums fs;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) fs.run[q] = 0.f;
+    fs.sum = 0.0;
+    fs.tiles = 0;
+    for (int b = it.b0; active && b < it.b1; ++b) {
+        const int s0 = a.src_ptr[b], s1 = a.src_ptr[b + 1];
+        const bool use = !(a.skip_same && body == b);
+        if (s1 == s0 || !__any(use)) continue;
+        const double x[3] = {(ct0 - a.far_centre[3 * b]) + (double)xt.x, (ct1 - a.far_centre[3 * b + 1]) + (double)xt.y,
+                             (ct2 - a.far_centre[3 * b + 2]) + (double)xt.z};
+        const float f0 = (float)x[0], f1 = (float)x[1], f2 = (float)x[2];
+        const float n2 = f0 * f0 + f1 * f1 + f2 * f2, rho = a.far_rho[b];
+        const bool far = n2 >= 4.0f * rho * rho && n2 > 1e-24f && n2 < 1e24f && use;  // false for NaN
+        if (__all(far)) {
+            far_body(a.far_tiles + 64 * (int64_t)a.far_tile_ptr[b], srcL + s0, s1 - s0, x, frag, str, fs);
+            continue;
+        }
+        const float xr[1][3] = {{xt.x + (float)(ct0 - a.centre[3 * b]), xt.y + (float)(ct1 - a.centre[3 * b + 1]),
+                                 xt.z + (float)(ct2 - a.centre[3 * b + 2])}};
+        for (int jb = s0; jb < s1; jb += FLUSH) {
+            const int cnt = min(FLUSH, s1 - jb);
+            float p[1] = {0.f};
+            if (lane < cnt) slot[lane] = srcL[jb + lane];
+            wave_lds_order();
+            int k = 0;
+            for (; k + 4 <= cnt; k += 4) laplace_pairs<1, 4>(xr, slot + k, p);
+            for (; k < cnt; ++k) laplace_pairs<1, 1>(xr, slot + k, p);
+            acc += use ? (double)p[0] : 0.0;
+            __builtin_amdgcn_wave_barrier();  // the next run's stores follow this run's reads
+        }
+    }
+    acc += far_total(fs, frag);
+    if (!valid) return;
+    double *out = a.out + (int64_t)it.split * a.out_stride;
+    const int64_t o = it.out0 + (idx - it.t0);
+    double v = a.alpha * it.scale * acc;
+    if (a.addend) v += a.addend[o];
+    if (a.accumulate) v += out[o];
+    out[o] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -414,6 +658,28 @@ __global__ __launch_bounds__(BLOCK) void p2p_mixed_kernel(KernelArgs a, const fl
     }
 }
 
+// The same for launches with far tiles (Laplace items of 256 targets).
+__global__ __launch_bounds__(BLOCK, 4) void p2p_far_kernel(KernelArgs a, const float4 *__restrict__ trg_off,
+                                                        const SrcL32 *__restrict__ srcL) {
+    __shared__ float4 stage[WAVES * 64];
+    __shared__ uint4v frag[WAVES * 256];
+    __shared__ float str[WAVES * 1024];
+    __shared__ int slot;
+    int k = blockIdx.x;
+    for (;;) {  // one item, or until the queue is empty
+        if (a.queue) {
+            __syncthreads();  // also orders the previous item's LDS reads before the next item's writes
+            if (threadIdx.x == 0) slot = atomicAdd(a.queue, 1);
+            __syncthreads();
+            k = slot;
+        }
+        if (k >= a.n_items) break;
+        const P2PItem it = a.items[k];
+        laplace_far_item(a, it, trg_off, srcL, stage, frag, str);
+        if (!a.queue) break;
+    }
+}
+
 template <int TPL>
 __global__ __launch_bounds__(BLOCK) void p2p_f64_kernel(KernelArgs a, const double4 *__restrict__ trg_off,
                                                         const SrcS64 *__restrict__ srcS,
@@ -446,6 +712,51 @@ __global__ void reduce_split_kernel(int64_t n, const double *__restrict__ partia
     if (addend) s += addend[v];
     if (accumulate) s += out[v];
     out[v] = s;
+}
+
+// Far centre (the mean of the body's sources), radius and tiles of every body; one workgroup per
+// body.  pos: [n][stride] from the body's base point (null: the origin).  A body with a source that
+// is not finite or further than 1e12 gets an infinite radius: no target is far from it.
+__global__ __launch_bounds__(256) void far_pack_kernel(const int32_t *__restrict__ ptr, const double *__restrict__ pos,
+                                                       int stride, const double *__restrict__ base,
+                                                       const int32_t *__restrict__ tile_ptr,
+                                                       double *__restrict__ centre, uint4v *__restrict__ tiles,
+                                                       float *__restrict__ rho) {
+    __shared__ double part[4][3];
+    __shared__ float sh[4];
+    const int b = blockIdx.x, s0 = ptr[b], n = ptr[b + 1] - s0;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const double *y = pos + stride * (int64_t)s0;
+    double c[3] = {0.0, 0.0, 0.0};
+    for (int j = threadIdx.x; j < n; j += 256)
+        for (int e = 0; e < 3; ++e) c[e] += y[stride * j + e];
+    for (int e = 0; e < 3; ++e) {
+        for (int d = 32; d > 0; d >>= 1) c[e] += __shfl_down(c[e], d, 64);
+        if (lane == 0) part[wv][e] = c[e];
+    }
+    __syncthreads();
+    for (int e = 0; e < 3; ++e) c[e] = (part[0][e] + part[1][e] + part[2][e] + part[3][e]) / max(n, 1);
+    float r2 = 0.f;
+    for (int j = threadIdx.x; j < n; j += 256) {
+        const double d[3] = {y[stride * j] - c[0], y[stride * j + 1] - c[1], y[stride * j + 2] - c[2]};
+        const double e = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+        r2 = fmaxf(r2, e <= 1e24 ? (float)e : __builtin_inff());
+    }
+    for (int d = 32; d > 0; d >>= 1) r2 = fmaxf(r2, __shfl_down(r2, d, 64));
+    if (lane == 0) sh[wv] = r2;
+    __syncthreads();
+    if (threadIdx.x == 0) rho[b] = 1.0001f * sqrtf(fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3])));
+    if (threadIdx.x < 3) {
+        const int e = threadIdx.x;
+        centre[3 * b + e] = (base ? base[3 * b + e] : 0.0) + (e == 0 ? c[0] : e == 1 ? c[1] : c[2]);
+    }
+    uint4v *t = tiles + 64 * (int64_t)tile_ptr[b];
+    const int nt = (n + 15) / 16;
+    for (int e = threadIdx.x; e < 64 * nt; e += 256) {
+        const double *yj = y + stride * min(far_source(e >> 6, nt, e & 63), n - 1);  // past the last: no strength
+        const double d[3] = {yj[0] - c[0], yj[1] - c[1], yj[2] - c[2]};
+        t[e] = pack_far_tile(d, e & 63);
+    }
 }
 
 __global__ void fill_ids_kernel(int64_t n_body, const int32_t *__restrict__ ptr, int32_t *__restrict__ ids) {
@@ -508,6 +819,7 @@ P2PItems items_of(const P2PPlan &pp) {
     it.n_items = (int)pp.items.size();
     it.n_split = pp.n_split;
     it.tpl = pp.tpl;
+    it.far = pp.far;
     it.persistent = pp.persistent;
     it.persistent_grid = pp.persistent_grid;
     it.counter = pp.d_counter.as<int>();
@@ -540,9 +852,15 @@ int launch_p2p(const P2PItems &pp, const P2PLaunch &L, hipStream_t s) {
     }
     if (L.ev_start) MFS_HIP_TRY(hipEventRecord(L.ev_start, s));
     if (L.prec == MFS_MIXED) {
+        a.far_tiles = (const uint4v *)L.far.tiles;
+        a.far_tile_ptr = L.far.tile_ptr;
+        a.far_centre = L.far.centre;
+        a.far_rho = L.far.rho;
         if (pp.tpl == 2)
             p2p_mixed_kernel<2><<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcS32 *)L.srcS,
                                                        (const SrcL32 *)L.srcL);
+        else if (pp.far)
+            p2p_far_kernel<<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcL32 *)L.srcL);
         else
             p2p_mixed_kernel<1><<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcS32 *)L.srcS,
                                                        (const SrcL32 *)L.srcL);
@@ -583,6 +901,15 @@ int launch_operands(const StandaloneOperands &o, int kind, int prec, hipStream_t
         if (kind == MFS_STOKES) operands_kernel<false, true><<<grid, 256, 0, s>>>(o);
         else operands_kernel<false, false><<<grid, 256, 0, s>>>(o);
     }
+    MFS_HIP_TRY(hipGetLastError());
+    return MFS_OK;
+}
+
+int launch_far_pack(int64_t n_body, const int32_t *ptr, const double *pos, int stride, const double *base,
+                    const FarTiles &far, hipStream_t s) {
+    if (n_body == 0) return MFS_OK;
+    far_pack_kernel<<<(unsigned)n_body, 256, 0, s>>>(ptr, pos, stride, base, far.tile_ptr, far.centre,
+                                                     (uint4v *)far.tiles, far.rho);
     MFS_HIP_TRY(hipGetLastError());
     return MFS_OK;
 }
