@@ -440,11 +440,10 @@ __device__ __forceinline__ void panel_registers(double *__restrict__ a, int m, i
 
 struct __attribute__((packed, aligned(8))) Rows4 { double v[4]; };  // four rows of a column
 
-// C[k0:m, cbase : min(cbase + 16, c1)] <- (I - V op(T) V^T) C, as wy_apply_kernel.  Lane l of a
+// C[k0:m, cbase : min(cbase + 16, c1)] <- (I - V T^T V^T) C, as wy_apply_kernel.  Lane l of a
 // 16-row block r0 holds rows r0 + 4 (l/16) + (0..3) of column l%16: the k slots of V^T C (MFMA u
 // takes row u of the four), and the D layout of V W when row i of the A operand there is row
 // 4 (i%4) + i/4 of the block.  Block b is wave b % QW's.
-template <bool TRANS>
 __device__ __forceinline__ void wy_update(const double *__restrict__ v, int m, int lda, int k0, int kb,
                                           const double *__restrict__ T, double *__restrict__ cm, int ldc, int cbase,
                                           int c1, QrShared &sh) {
@@ -502,14 +501,10 @@ __device__ __forceinline__ void wy_update(const double *__restrict__ v, int m, i
         sh.Pw[0][i][j] = p;
     }
     __syncthreads();
-    if (t < NB * CT) {  // 2. W = op(T) P
+    if (t < NB * CT) {  // 2. W = T^T P
         const int i = t / CT, j = t % CT;
         double s = 0.0;
-        if (TRANS) {
-            for (int l = 0; l <= i; ++l) s += sh.Ts[l][i] * sh.Pw[0][l][j];
-        } else {
-            for (int l = i; l < NB; ++l) s += sh.Ts[i][l] * sh.Pw[0][l][j];
-        }
+        for (int l = 0; l <= i; ++l) s += sh.Ts[l][i] * sh.Pw[0][l][j];
         sh.W[i][j] = s;
     }
     __syncthreads();
@@ -581,20 +576,133 @@ __global__ __launch_bounds__(QT) void qr_step_kernel(double *__restrict__ A, int
     __shared__ QrShared sh;
     const int b = blockIdx.y, c = k0 + NB + (int)blockIdx.x * CT;
     double *a = A + (int64_t)b * stride;
-    wy_update<true>(a, m, m, k0, NB, Tp + (int64_t)b * NB * NB, a, m, c, n, sh);
+    wy_update(a, m, m, k0, NB, Tp + (int64_t)b * NB * NB, a, m, c, n, sh);
     if (blockIdx.x != 0) return;  // uniform over the workgroup
     __syncthreads();              // the updated columns are read back in the panel's layout
     panel_registers<RPT>(a, m, m, c, min(NB, n - c), tau + (int64_t)b * n, Tnext + (int64_t)b * NB * NB, sh);
 }
 
-// Q <- (I - V T V^T) Q on rows k0..m-1 of columns k0..n-1.
-__global__ __launch_bounds__(QT) void q_step_kernel(const double *__restrict__ A, int m, int64_t stride_a, int k0, int kb,
-                                                    const double *__restrict__ Tp, double *__restrict__ Q,
-                                                    int64_t stride_q, int n) {
+// 16 columns of Q = H_0 H_1 ... [I; 0] in one workgroup's registers through all panels that reach
+// them (panel p touches columns 16 p and later), last panel first.  Block b (rows 16 b ..) is wave
+// b % QW's slot b / QW, in the layout of wy_update: V^T C and C - V W both take it as it lies, so
+// only V moves (twice per panel, from L2).  A launch per panel with C in memory took 38 us a panel,
+// 2.8 ms for 2400 x 1200; now 1.55.
+template <int RPT>
+__global__ __launch_bounds__(QT) void q_kernel(const double *__restrict__ A, int m, int64_t stride_a, int n,
+                                               const double *__restrict__ Tall, int batch, double *__restrict__ Q,
+                                               int64_t stride_q) {
+    constexpr int SLOTS = RPT * QT / 16 / QW, GR = 4;  // blocks per wave, blocks in flight
     __shared__ QrShared sh;
-    const int b = blockIdx.y;
-    wy_update<false>(A + (int64_t)b * stride_a, m, m, k0, kb, Tp + (int64_t)b * NB * NB, Q + (int64_t)b * stride_q, m,
-                     k0 + (int)blockIdx.x * CT, n, sh);
+    const int t = threadIdx.x, lane = t & 63, q = lane >> 4, c16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int cb = (int)(gridDim.x - 1 - blockIdx.x), b = blockIdx.y;  // the longest chains first
+    const int col = 16 * cb + c16;
+    const int blocks = (m + 15) / 16, whole = m / 16;
+    const double *a = A + (int64_t)b * stride_a;
+    const int rho = 4 * (c16 & 3) + (c16 >> 2);
+    doublex4 C[SLOTS];
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) C[i][u] = 16 * (wave + QW * i) + 4 * q + u == col ? 1.0 : 0.0;
+#pragma unroll 1
+    for (int p = cb; p >= 0; --p) {
+        const int k0 = 16 * p, kb = min(NB, n - k0);
+        const bool vok = c16 < kb;
+        const double *vcol = a + (int64_t)(k0 + (vok ? c16 : 0)) * m + 4 * q;
+        if (t < NB * NB) sh.Ts[t / NB][t % NB] = Tall[((int64_t)p * batch + b) * NB * NB + t];
+        doublex4 acc[2] = {};  // P = V^T C
+#pragma unroll
+        for (int g = 0; g < SLOTS; g += GR) {
+            if (wave + QW * (g + GR - 1) < p || wave + QW * g >= blocks) continue;
+            Rows4 x[GR];
+#pragma unroll
+            for (int i = 0; i < GR; ++i) {
+                const int bl = wave + QW * (g + i);
+                if (bl < whole) {  // blocks before the panel's are read and count as zero
+                    x[i] = *reinterpret_cast<const Rows4 *>(vcol + 16 * bl);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) x[i].v[u] = 16 * bl + 4 * q + u < m ? vcol[16 * bl + u] : 0.0;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < GR; ++i) {
+                const int bl = wave + QW * (g + i);
+                if (bl < p) continue;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    double y = vok ? x[i].v[u] : 0.0;
+                    if (bl == p) {  // the unit lower triangle
+                        const int r = 4 * q + u;
+                        y = (r < c16 || !vok) ? 0.0 : (r == c16 ? 1.0 : y);
+                    }
+                    acc[u & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(y, C[g + i][u], acc[u & 1], 0, 0, 0);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sh.Pw[wave][q + 4 * r][c16] = acc[0][r] + acc[1][r];
+        __syncthreads();
+        if (t < NB * CT) {  // P summed over the waves in order
+            const int i = t / CT, j = t % CT;
+            double s = sh.Pw[0][i][j];
+#pragma unroll
+            for (int w = 1; w < QW; ++w) s += sh.Pw[w][i][j];
+            sh.Pw[0][i][j] = s;
+        }
+        __syncthreads();
+        if (t < NB * CT) {  // -W = -T P
+            const int i = t / CT, j = t % CT;
+            double s = 0.0;
+            for (int l = i; l < NB; ++l) s -= sh.Ts[i][l] * sh.Pw[0][l][j];
+            sh.W[i][j] = s;
+        }
+        __syncthreads();
+        double wv[4];
+        const double *vk[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            wv[u] = sh.W[4 * u + q][c16];
+            vk[u] = a + (int64_t)(k0 + min(4 * u + q, kb - 1)) * m + rho;
+        }
+#pragma unroll
+        for (int g = 0; g < SLOTS; g += GR) {  // C -= V W
+            if (wave + QW * (g + GR - 1) < p || wave + QW * g >= blocks) continue;
+            double x[GR][4];
+#pragma unroll
+            for (int i = 0; i < GR; ++i) {
+                const int bl = wave + QW * (g + i);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[i][u] = 16 * bl + rho < m ? vk[u][16 * bl] : 0.0;
+            }
+#pragma unroll
+            for (int i = 0; i < GR; ++i) {
+                const int bl = wave + QW * (g + i);
+                if (bl < p) continue;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int k = 4 * u + q;
+                    double y = k < kb ? x[i][u] : 0.0;
+                    if (bl == p) y = (rho < k || k >= kb) ? 0.0 : (rho == k ? 1.0 : y);
+                    C[g + i] = __builtin_amdgcn_mfma_f64_16x16x4f64(y, wv[u], C[g + i], 0, 0, 0);
+                }
+            }
+        }
+    }
+    if (col >= n) return;
+    double *o = Q + (int64_t)b * stride_q + (int64_t)col * m + 4 * q;
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) {
+        const int bl = wave + QW * i;
+        if (bl < whole) {
+            *reinterpret_cast<Rows4 *>(o + 16 * bl) = Rows4{{C[i][0], C[i][1], C[i][2], C[i][3]}};
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (16 * bl + 4 * q + u < m) o[16 * bl + u] = C[i][u];
+        }
+    }
 }
 
 template <class F>
@@ -658,6 +766,111 @@ __global__ __launch_bounds__(FB) void upper_inverse_kernel(const double *__restr
     }
 }
 
+// The same for 16 columns per workgroup with the right-hand sides in registers (as in q_kernel):
+// block row p of X is a 16 x 16 substitution, which every wave does for itself, and goes into the rows
+// above on the matrix cores; one barrier per block row where the kernel above has two per row.
+// n = 1200: 1.0 -> 0.37 ms.
+struct InverseShared {
+    double c[2][NB][CT];       // the right-hand sides of a block row
+    double R[2][NB][NB + 1];   // its diagonal block
+    double x[QW][NB][CT];      // a wave's solution, to be read in the B layout
+};
+template <int RPT>
+__global__ __launch_bounds__(QT) void inverse_kernel(const double *__restrict__ R, int n, int ldr, int64_t stride_r,
+                                                     double *__restrict__ X, int ldx, int64_t stride_x,
+                                                     double *__restrict__ colsq) {
+    constexpr int SLOTS = RPT * QT / 16 / QW, GR = 4;
+    __shared__ InverseShared sh;
+    const int t = threadIdx.x, lane = t & 63, q = lane >> 4, c16 = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int cb = (int)(gridDim.x - 1 - blockIdx.x), b = blockIdx.y;  // the longest chains first
+    const int col = 16 * cb + c16;
+    const double *Rb = R + (int64_t)b * stride_r;
+    double *Xb = X + (int64_t)b * stride_x;
+    const int rho = 4 * (c16 & 3) + (c16 >> 2);
+    doublex4 C[SLOTS];
+#pragma unroll
+    for (int i = 0; i < SLOTS; ++i) C[i] = doublex4{0.0, 0.0, 0.0, 0.0};
+    // element (r, k) of the diagonal block p; the unit matrix past the last column
+    auto diagonal = [&](int p) {
+        const int r = t & 15, k = t >> 4, row = 16 * p + r, cl = 16 * p + k;
+        return row < n && cl < n ? (r <= k ? Rb[(int64_t)cl * ldr + row] : 0.0) : (r == k ? 1.0 : 0.0);
+    };
+    if (t < NB * NB) {
+        sh.R[cb & 1][t & 15][t >> 4] = diagonal(cb);
+        sh.c[cb & 1][t & 15][t >> 4] = (t & 15) == (t >> 4) ? 1.0 : 0.0;
+    }
+    double sx = 0.0;
+#pragma unroll 1
+    for (int p = cb; p >= 0; --p) {
+        __syncthreads();
+        const double next = p > 0 && t < NB * NB ? diagonal(p - 1) : 0.0;
+        const double *rk = Rb + rho;
+        auto load = [&](double (&y)[GR][4], int g) {
+#pragma unroll
+            for (int i = 0; i < GR; ++i) {
+                const int bl = wave + QW * (g + i);
+                if (bl < p)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) y[i][u] = rk[(int64_t)min(16 * p + 4 * u + q, n - 1) * ldr + 16 * bl];
+            }
+        };
+        double y[GR][4];
+        load(y, 0);
+        double x[NB];
+#pragma unroll
+        for (int r = 0; r < NB; ++r) x[r] = sh.c[p & 1][r][c16];
+        const double inv = 1.0 / sh.R[p & 1][c16][c16];
+#pragma unroll
+        for (int r = NB - 1; r >= 0; --r) {
+            x[r] *= lane_value(inv, r);
+#pragma unroll
+            for (int a = 0; a < r; ++a) x[a] -= sh.R[p & 1][a][r] * x[r];
+        }
+#pragma unroll
+        for (int r = 0; r < NB; ++r) sx += x[r] * x[r];
+        if (q == 0)
+#pragma unroll
+            for (int r = 0; r < NB; ++r) sh.x[wave][r][c16] = x[r];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // a wave's LDS accesses complete in order
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (wave == p % QW && col < n)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (16 * p + 4 * q + u < n) Xb[(int64_t)col * ldx + 16 * p + 4 * q + u] = sh.x[wave][4 * q + u][c16];
+        double wv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) wv[u] = -sh.x[wave][4 * u + q][c16];
+#pragma unroll
+        for (int g = 0; g < SLOTS; g += GR) {
+            if (wave + QW * g >= p) continue;
+            if (g > 0) load(y, g);
+#pragma unroll
+            for (int i = 0; i < GR; ++i) {
+                const int bl = wave + QW * (g + i);
+                if (bl >= p) continue;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) C[g + i] = __builtin_amdgcn_mfma_f64_16x16x4f64(y[i][u], wv[u], C[g + i], 0, 0, 0);
+                if (bl == p - 1)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) sh.c[bl & 1][4 * q + u][c16] = C[g + i][u];
+            }
+        }
+        if (p > 0 && t < NB * NB) sh.R[(p - 1) & 1][t & 15][t >> 4] = next;
+    }
+    if (wave == 0 && q == 0 && col < n) colsq[(int64_t)b * 2 * n + n + col] = sx;
+    for (int j = wave; j < CT; j += QW) {  // rows past the block row's, and the squares of R's column
+        const int cj = 16 * cb + j;
+        if (cj >= n) break;
+        for (int r = 16 * (cb + 1) + lane; r < n; r += 64) Xb[(int64_t)cj * ldx + r] = 0.0;
+        double sr = 0.0;
+        for (int r = lane; r <= cj; r += 64) sr += Rb[(int64_t)cj * ldr + r] * Rb[(int64_t)cj * ldr + r];
+        for (int d = 32; d > 0; d >>= 1) sr += __shfl_down(sr, d, 64);
+        if (lane == 0) colsq[(int64_t)b * 2 * n + cj] = sr;
+    }
+}
+
 // ratio[b] = 1 / (||R||_F ||R^-1||_F), a lower bound of sigma_min / sigma_max
 __global__ __launch_bounds__(FB) void qr_ratio_kernel(int n, const double *__restrict__ colsq, double *__restrict__ ratio) {
     __shared__ double sh[FB / 64];
@@ -711,19 +924,27 @@ int qr_inverse_batched(int batch, double *A, int m, int n, int64_t stride_a, dou
         }
     }
     MFS_HIP_TRY(hipGetLastError());
-    const int64_t total = (int64_t)batch * m * n;
-    identity_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(Q, m, n, stride_q, total);
-    for (int p = panels - 1; p >= 0; --p) {
-        const int k0 = p * NB, kb = std::min(NB, n - k0);
-        const dim3 grid((n - k0 + CT - 1) / CT, batch);
-        if (in_registers)
-            q_step_kernel<<<grid, QT, 0, s>>>(A, m, stride_a, k0, kb, panel_T(p), Q, stride_q, n);
-        else
-            wy_apply_kernel<false><<<grid, FB, 0, s>>>(A, m, m, stride_a, k0, kb, panel_T(p), Q, m, stride_q, k0, n);
+    if (in_registers) {
+        with_rows(m, [&](auto R) {
+            q_kernel<R.value><<<dim3(panels, batch), QT, 0, s>>>(A, m, stride_a, n, Tall, batch, Q, stride_q);
+        });
+    } else {
+        const int64_t total = (int64_t)batch * m * n;
+        identity_kernel<<<(unsigned)((total + 255) / 256), 256, 0, s>>>(Q, m, n, stride_q, total);
+        for (int p = panels - 1; p >= 0; --p) {
+            const int k0 = p * NB, kb = std::min(NB, n - k0);
+            wy_apply_kernel<false><<<dim3((n - k0 + CT - 1) / CT, batch), FB, 0, s>>>(
+                A, m, m, stride_a, k0, kb, panel_T(p), Q, m, stride_q, k0, n);
+        }
     }
     MFS_HIP_TRY(hipGetLastError());
-    upper_inverse_kernel<<<dim3(n, batch), FB, (size_t)n * sizeof(double), s>>>(A, n, m, stride_a, X, n, stride_x,
-                                                                               colsq);
+    if (in_registers)
+        with_rows(n, [&](auto R) {
+            inverse_kernel<R.value><<<dim3(panels, batch), QT, 0, s>>>(A, n, m, stride_a, X, n, stride_x, colsq);
+        });
+    else
+        upper_inverse_kernel<<<dim3(n, batch), FB, (size_t)n * sizeof(double), s>>>(A, n, m, stride_a, X, n, stride_x,
+                                                                                   colsq);
     qr_ratio_kernel<<<batch, FB, 0, s>>>(n, colsq, ratio);
     MFS_HIP_TRY(hipGetLastError());
     return MFS_OK;

@@ -7,6 +7,7 @@ in oracle/fp32_model.py)."""
 import numpy as np
 import pytest
 import torch
+from scipy.linalg import solve_triangular
 
 import mfs_workloads as W
 from oracle import fp32_model as M
@@ -32,4 +33,24 @@ def test_qr_sizes(kind, n, m):
     plan.close()
     e = rel_inf(got, ref)
     print(f"kind={kind} n={n} m={m} err={e:.2e} bar={bar:.2e}")
+    assert e <= bar
+
+
+@pytest.mark.parametrize("n,m", [(513, 1025), (1025, 1537), (1537, 2560), (2049, 2560)])
+def test_qr_many_columns(n, m):
+    """Columns at the edges of the rows per thread of R^-1: the strengths from S_L c on one body, with the bar of a
+    float64 Householder QR and explicit R^-1 (4 x its error)."""
+    from paper_2409_04215_amd import mfs
+    wl = W.small_cluster(1, W.LAPLACE, n, m, seed=173)
+    pr = O.Problem.from_workload(wl)
+    S = pr.one_body_matrix(wl.shapes[0].trg, wl.shapes[0].src, np.zeros(3))  # S_L
+    c = W.random_vector(n, 174)
+    g = S @ c
+    q, r = np.linalg.qr(S)
+    own = solve_triangular(r, np.eye(n)) @ (q.T @ g)
+    plan = mfs.Plan.from_workload(wl, mfs.FP64, factorization=mfs.FACTOR_QR)
+    got = plan.precond_apply(torch.tensor(g, dtype=torch.float64, device="cuda"), 0, mfs.FP64).cpu().numpy()
+    plan.close()
+    e, bar = rel_inf(got, c), M.bar(rel_inf(own, c))
+    print(f"n={n} m={m} err={e:.2e} bar={bar:.2e}")
     assert e <= bar
