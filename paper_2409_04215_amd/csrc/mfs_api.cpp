@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <mutex>
 #include <numeric>
@@ -204,6 +205,29 @@ bool use_far_tiles(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *bo
     return most >= 32 && pairs >= 2.5e8 && 16.0 * (double)tiles <= 1.25 * (double)sources;
 }
 
+// Whether a standalone mixed sum takes wide items (p2p_wide_kernel: 16 waves on 64 targets and every
+// source of their system, one launch): when that many workgroups fit the chip at once and the longest
+// of them, S sources on one CU (its waves share the LDS that they read the sources from: 7.7 ns a
+// Stokes source, 3.5 Laplace), takes no more than the sum on all CUs plus the launches saved.  Both
+// sides, us: Stokes 4 bodies of 300 x 600 25.7 general, 19.1 wide; 6 of 400 x 800 24.2, 24.8; 10 of
+// 300 x 600 24.7, 29.3; Laplace 20 of 400 x 800 39.6, 32.9; 6 of 200 x 400 in 6 systems 24.6, 21.3.
+bool use_wide_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
+                    const int64_t *body_src_ptr, int kind) {
+    constexpr double saved_us = 11.0;
+    const bool stokes = kind == MFS_STOKES;
+    int64_t blocks = 0;
+    double longest = 0.0, all = 0.0;  // us
+    for (int64_t sy = 0; sy < n_sys; ++sy) {
+        const int64_t b0 = sys_body_ptr[sy], b1 = sys_body_ptr[sy + 1];
+        const int64_t nt = body_trg_ptr[b1] - body_trg_ptr[b0], ns = body_src_ptr[b1] - body_src_ptr[b0];
+        if (nt == 0) continue;
+        blocks += (nt + 63) / 64;
+        longest = std::max(longest, (double)ns * (stokes ? 7.7e-3 : 3.5e-3));
+        all += (double)nt * (double)ns / (stokes ? 2.9e6 : 5.7e6);
+    }
+    return blocks <= 256 && longest <= all + saved_us;
+}
+
 int build_p2p_items(P2PPlan &pp, int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                     const int64_t *body_src_ptr, const int64_t *out_ptr, const int32_t *kind_of_body, double mu,
                     int tpl, int min_items, hipStream_t s, bool far) {
@@ -245,7 +269,7 @@ struct Layout {
     std::vector<int32_t> trg32, src32, tiles_h;
     DevBuf trg_ptr, src_ptr, trg_body, src_body;
     P2PPlan pp;
-    bool far_ok = false, far = false;  // far tiles: allowed, used
+    bool mixed = false, far = false;  // a mixed pair sum; far tiles used
     int64_t n_tiles = 0;
     DevBuf tile_ptr;
     uint64_t last_use = 0;
@@ -311,14 +335,14 @@ int check_prec(int prec) {
 
 // The cached layout of (variant, mu, structure), built if missing.  kind sets
 // the items' kernel and scale; dim the output values per target of the items.
-// far_ok: the launch can take far tiles.
+// mixed: a mixed pair sum that can take far tiles or wide items.
 int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_sys, const int64_t *sys_body_ptr,
            const int64_t *body_trg_ptr, const int64_t *body_src_ptr, int64_t nb, hipStream_t s, Layout **out,
-           bool far_ok = false) {
+           bool mixed = false) {
     uint64_t bits;
     std::memcpy(&bits, &mu, sizeof bits);
     auto same = [&](const Layout &l) {
-        return l.variant == variant && l.far_ok == far_ok && l.mu_bits == bits && (int64_t)l.sys.size() == n_sys + 1 &&
+        return l.variant == variant && l.mixed == mixed && l.mu_bits == bits && (int64_t)l.sys.size() == n_sys + 1 &&
                (int64_t)l.trg.size() == nb + 1 && (int64_t)l.src.size() == nb + 1 &&
                std::equal(l.sys.begin(), l.sys.end(), sys_body_ptr) &&
                std::equal(l.trg.begin(), l.trg.end(), body_trg_ptr) &&
@@ -341,7 +365,7 @@ int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_s
     }
     auto l = std::make_unique<Layout>();
     l->variant = variant;
-    l->far_ok = far_ok;
+    l->mixed = mixed;
     l->mu_bits = bits;
     l->sys.assign(sys_body_ptr, sys_body_ptr + n_sys + 1);
     l->trg.assign(body_trg_ptr, body_trg_ptr + nb + 1);
@@ -360,14 +384,16 @@ int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_s
     const int min_items = default_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, kind,
                                             kStandaloneMinItems);
     std::vector<int32_t> tiles;
-    l->far = far_ok && use_far_tiles(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, tiles);
+    l->far = mixed && kind == MFS_LAPLACE && use_far_tiles(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, tiles);
     if (l->far) {
         l->tiles_h.swap(tiles);
         l->n_tiles = l->tiles_h.back();
         MFS_TRY(upload_vec(l->tile_ptr, l->tiles_h, s));
     }
+    const bool wide = variant == kind && mixed && use_wide_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, kind);
     MFS_TRY(build_p2p_items(l->pp, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, out_ptr.data(), kob.data(), mu, 1,
-                            min_items, s, l->far));
+                            wide ? 1 : min_items, s, l->far));
+    l->pp.wide = wide;
     l->last_use = ++ws.clock;
     *out = l.get();
     ws.layouts.push_back(std::move(l));
@@ -426,6 +452,16 @@ int standalone_partial(Workspace &ws, const Layout &lay, P2PLaunch &L) {
     return MFS_OK;
 }
 
+// Whether the output shares memory with an input, which wide items would read while it is written.
+bool overlaps_inputs(const double *out, int64_t n_out, const double *trg, const double *src, const double *str,
+                     int64_t n_trg, int64_t n_src, int dim) {
+    auto meets = [&](const double *p, int64_t n) {
+        const std::less<const double *> before;
+        return n > 0 && n_out > 0 && before(p, out + n_out) && before(out, p + n);
+    };
+    return meets(trg, 3 * n_trg) || meets(src, 3 * n_src) || meets(str, dim * n_src);
+}
+
 int p2p_standalone(int kind, int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                    const int64_t *body_src_ptr, const double *trg_xyz, const double *src_xyz, const double *str,
                    double *out, double mu, int flags, int prec, void *stream) {
@@ -442,9 +478,18 @@ int p2p_standalone(int kind, int64_t n_sys, const int64_t *sys_body_ptr, const i
     const int dim = kind == MFS_STOKES ? 3 : 1;
     Layout *lay = nullptr;
     MFS_TRY(layout(ws, kind, kind, dim, mu, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nb, s, &lay,
-                   kind == MFS_LAPLACE && prec == MFS_MIXED));
+                   prec == MFS_MIXED && !overlaps_inputs(out, dim * nt, trg_xyz, src_xyz, str, nt, ns, dim)));
     P2PLaunch L;
-    MFS_TRY(standalone_operands(ws, *lay, kind, nb, nt, ns, trg_xyz, src_xyz, str, prec, s, L));
+    if (lay->pp.wide) {
+        L.prec = prec;
+        L.trg_body = lay->trg_body.as<int32_t>();
+        L.src_ptr = lay->src_ptr.as<int32_t>();
+        L.raw_trg = trg_xyz;
+        L.raw_src = src_xyz;
+        L.raw_str = str;
+    } else {
+        MFS_TRY(standalone_operands(ws, *lay, kind, nb, nt, ns, trg_xyz, src_xyz, str, prec, s, L));
+    }
     L.skip_same = (flags & MFS_SKIP_SAME_BODY) != 0;
     L.accumulate = (flags & MFS_ACCUMULATE) != 0;
     L.out = out;
@@ -1187,6 +1232,12 @@ int p2p_stokes_noalloc(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
     if (need > kScratchBytes)
         return fail(MFS_EINVAL, "mfs_p2p_stokes_noalloc needs " + std::to_string(need) +
                                     " bytes of scratch for these sizes; it holds " + std::to_string(kScratchBytes));
+    // checked above on the general items, so that what is refused does not depend on the walk
+    const bool wide = f32 && use_wide_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, MFS_STOKES) &&
+                      !overlaps_inputs(out, 3 * nt, trg_xyz, src_xyz, str, nt, ns, 3);
+    if (wide)
+        MFS_TRY(generate_p2p_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, 3, nullptr, MFS_STOKES, mu,
+                                   1, 1, h.items, h.work, h.order, h.sorted, kNoAllocMaxItems, &n_items, &n_split));
     void *base = nullptr;
     MFS_TRY(scratch_address(&base));
     unsigned char *q = static_cast<unsigned char *>(base);
@@ -1230,9 +1281,10 @@ int p2p_stokes_noalloc(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
     o.centre = d_centre;
     o.trg_off = d_trg_off;
     o.src_ops = d_src_ops;
-    MFS_TRY(launch_operands(o, MFS_STOKES, prec, s));
+    if (!wide) MFS_TRY(launch_operands(o, MFS_STOKES, prec, s));
     P2PItems it;
     it.items = d_items;
+    it.wide = wide;
     it.n_items = (int)n_items;
     it.n_split = n_split;
     it.tpl = 1;
@@ -1245,6 +1297,11 @@ int p2p_stokes_noalloc(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
     L.src_ptr = d_src_ptr;
     L.trg_off = d_trg_off;
     L.srcS = d_src_ops;
+    if (wide) {
+        L.raw_trg = trg_xyz;
+        L.raw_src = src_xyz;
+        L.raw_str = str;
+    }
     L.out = out;
     L.partial = d_partial;
     L.n_val = 3 * nt;

@@ -115,6 +115,8 @@ struct P2PLaunch {
     const void *srcS = nullptr;           // SrcS32 / SrcS64 [n_src] (Stokes bodies)
     const void *srcL = nullptr;           // SrcL32 / SrcL64 [n_src] (Laplace bodies)
     FarTiles far;                         // mixed Laplace sums of one target per lane
+    // wide items of a standalone sum take the caller's points instead of centre, trg_off, srcS and srcL
+    const double *raw_trg = nullptr, *raw_src = nullptr, *raw_str = nullptr;
     double *out = nullptr;                // final output [n_val]
     double *partial = nullptr;            // [n_split][n_val] when n_split > 1
     const double *addend = nullptr;       // added once to the output (may be null)
@@ -129,6 +131,7 @@ struct P2PPlan {
     int n_split = 1;
     int tpl = 1;
     bool far = false;            // Laplace items of 256 targets for the far walk (tpl 1)
+    bool wide = false;           // workgroups of 16 waves on 64 targets (standalone mixed, tpl 1, n_split 1)
     bool persistent = false;     // fixed grid + work-queue counter instead of one workgroup per item
     int persistent_grid = 2048;  // workgroups of a persistent launch
     DevBuf d_items;
@@ -159,7 +162,7 @@ struct P2PItems {
     int n_items = 0;
     int n_split = 1;
     int tpl = 1;
-    bool far = false;
+    bool far = false, wide = false;
     bool persistent = false;
     int persistent_grid = 2048;
     int *counter = nullptr;  // persistent mode only
