@@ -19,7 +19,6 @@ namespace mfs {
 // kernels declared here to keep the internal header short
 int launch_make_factor(int rows, int cols, const double *src, int64_t ld, bool transposed, const double *rs,
                        const double *cs, double *d64, float *d32, hipStream_t s);
-int launch_p2p_grad(const P2PPlan &pp, const P2PLaunch &L, const double *lane_vec, int64_t n_lane, hipStream_t s);
 
 // ---------------------------------------------------------------------------
 // errors
@@ -527,10 +526,12 @@ int field_standalone(int field, int64_t n_sys, const int64_t *sys_body_ptr, cons
 }
 
 // Position gradient of the pairing over one orientation: lanes carry lane_vec
-// ([n_lane][dim]), sources carry src_str; out_grad [n_lane][3].
+// ([n_lane][dim]), sources carry src_str; out_grad [n_lane][3].  out_sum (or null): the sum of the
+// sources at the lanes as well, [n_lane][dim].
 int p2p_grad_standalone(int kind, int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *lane_ptr,
                         const int64_t *src_ptr, const double *lane_xyz, const double *src_xyz, const double *lane_vec,
-                        const double *src_str, double *out_grad, double mu, int flags, int prec, hipStream_t s) {
+                        const double *src_str, double *out_grad, double *out_sum, double mu, int flags, int prec,
+                        hipStream_t s) {
     const int64_t nb = sys_body_ptr[n_sys], nl = lane_ptr[nb], ns = src_ptr[nb];
     if (nl == 0) return MFS_OK;
     Workspace &ws = workspace();
@@ -542,9 +543,9 @@ int p2p_grad_standalone(int kind, int64_t n_sys, const int64_t *sys_body_ptr, co
     L.skip_same = (flags & MFS_SKIP_SAME_BODY) != 0;
     L.accumulate = (flags & MFS_ACCUMULATE) != 0;
     L.out = out_grad;
-    L.n_val = 3 * nl;
+    L.n_val = 3 * nl + (out_sum ? dim * nl : 0);  // values of a split slice
     MFS_TRY(standalone_partial(ws, *lay, L));
-    return launch_p2p_grad(lay->pp, L, lane_vec, nl, s);
+    return launch_p2p_grad(lay->pp, L, lane_vec, nl, s, out_sum, dim * nl);
 }
 
 int p2p_backward_standalone(int kind, int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
@@ -559,15 +560,15 @@ int p2p_backward_standalone(int kind, int64_t n_sys, const int64_t *sys_body_ptr
     if ((nt > 0 && (!trg_xyz || !trg_w)) || (ns > 0 && (!src_xyz || !src_s)))
         return fail(MFS_EINVAL, "NULL data pointer");
     hipStream_t s = (hipStream_t)stream;
-    if (grad_src)  // dPhi/ds_j = sum_i G(y_j - x_i) w_i: the sum with the roles swapped
+    if (grad_src && !grad_src_xyz)  // dPhi/ds_j = sum_i G(y_j - x_i) w_i: the sum with the roles swapped
         MFS_TRY(p2p_standalone(kind, n_sys, sys_body_ptr, body_src_ptr, body_trg_ptr, src_xyz, trg_xyz, trg_w, grad_src,
                                mu, flags, prec, stream));
     if (grad_trg_xyz)
         MFS_TRY(p2p_grad_standalone(kind, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, src_xyz, trg_w,
-                                    src_s, grad_trg_xyz, mu, flags, prec, s));
-    if (grad_src_xyz)  // odd, symmetric pair term: the same kernel on the swapped orientation
+                                    src_s, grad_trg_xyz, nullptr, mu, flags, prec, s));
+    if (grad_src_xyz)  // odd, symmetric pair term: the same kernel on the swapped orientation, dPhi/ds_j on the way
         MFS_TRY(p2p_grad_standalone(kind, n_sys, sys_body_ptr, body_src_ptr, body_trg_ptr, src_xyz, trg_xyz, src_s,
-                                    trg_w, grad_src_xyz, mu, flags, prec, s));
+                                    trg_w, grad_src_xyz, grad_src, mu, flags, prec, s));
     return MFS_OK;
 }
 

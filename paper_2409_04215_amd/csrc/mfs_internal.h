@@ -192,7 +192,8 @@ int launch_fill_body_ids(int64_t n_body, const int32_t *ptr, int32_t *ids, hipSt
 
 // Position gradients of the pair sums (p2p_backward.hip): lane vectors indexed like the
 // forward output, gradient [n_lane][3].
-int launch_p2p_grad(const P2PPlan &pp, const P2PLaunch &L, const double *lane_vec, int64_t n_lane, hipStream_t s);
+int launch_p2p_grad(const P2PPlan &pp, const P2PLaunch &L, const double *lane_vec, int64_t n_lane, hipStream_t s,
+                    double *sum_out = nullptr, int64_t n_sum = 0);
 
 // Derived fields of the representation (field_kernels.hip): items of one target
 // per lane; L.srcS (pressure, traction) or L.srcL (Laplace gradient) hold the
