@@ -18,10 +18,10 @@
 //     P = V^T C, W = T^T P, C -= V W, both products on the FP64 matrix cores
 //     (v_mfma_f64_16x16x4f64); one workgroup per 16 columns.
 // Q = H_0 H_1 ... H_{n-1} [I; 0] is accumulated panel by panel from the last
-// one with the same kernel (C <- (I - V T V^T) C on rows k0..m-1 of columns
+// one in the same way (C <- (I - V T V^T) C on rows k0..m-1 of columns
 // k0..n-1; earlier columns of Q are still unit vectors there), and
-// X = R^-1 comes from n independent triangular solves R x_i = e_i, one
-// workgroup per column, with the running sums in LDS.
+// X = R^-1 comes from n independent triangular solves R x_i = e_i.  These are
+// the kernels for many rows; most matrices take the ones further down.
 // Reductions add in a fixed order: results do not depend on timing.
 #include <algorithm>
 #include <type_traits>
@@ -265,10 +265,12 @@ __global__ __launch_bounds__(FB) void wy_apply_kernel(const double *__restrict__
 //    (200 KB of code, run once, took 129 us per panel in instruction fetches);
 //  * the WY update has six blocks of rows in flight per wave;
 //  * one launch per panel: workgroup 0 updates the next panel's columns and
-//    factors them, the others update the rest meanwhile.
-// 2400 x 1200 (QR, Q and R^-1): 32.0 ms before, 9.1 ms now (a panel 41 us, a WY update
-// 38 us), plan creation 34.7 -> 11.7 ms.  sqrt and the divisions are not what a column
-// step waits for: through v_rsq_f64 and v_rcp_f64 a panel took the same 40 us.
+//    factors them, both in the panel's registers, the others update the rest
+//    meanwhile (52 to 67 us a step);
+//  * Q and R^-1 are one launch each, 16 columns per workgroup in registers.
+// 2400 x 1200 (QR, Q and R^-1): 32.0 ms before, 6.4 ms now (4.4, 1.55 and 0.37), plan
+// creation 34.7 -> 9.2 ms.  sqrt and the divisions are not what a column step waits
+// for: through v_rsq_f64 and v_rcp_f64 a panel took the same 40 us.
 // ---------------------------------------------------------------------------
 constexpr int QT = 512;        // threads
 constexpr int QW = QT / 64;    // waves
@@ -335,24 +337,111 @@ __device__ __forceinline__ double wave_sums16(double (&v)[16], int lane) {
     return r;
 }
 
-// Factors the panel at k0 (kb columns, rows k0..m-1 in registers: thread t holds rows
-// k0 + t + QT i) and forms T, as panel_qr_kernel does.  At step j the registers hold the
-// columns j, j+1, ..., 15, 0, ..., j-1, the last j of them reflectors already.
+// The panel at k0 (kb columns, rows k0..m-1) in registers: thread t holds rows k0 + t + QT i.
 template <int RPT>
-__device__ __forceinline__ void panel_registers(double *__restrict__ a, int m, int lda, int k0, int kb,
-                                                double *__restrict__ tau, double *__restrict__ T, QrShared &sh) {
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, ql = lane >> 2;
+__device__ __forceinline__ void panel_load(const double *__restrict__ a, int m, int lda, int k0, int kb,
+                                           double (&X)[RPT][NB]) {
     const unsigned rows = (unsigned)(m - k0);
-    double X[RPT][NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
         const double *x = a + (int64_t)(k0 + (q < kb ? q : 0)) * lda + k0;
 #pragma unroll
         for (int i = 0; i < RPT; ++i) {
-            const unsigned r = t + QT * i;
+            const unsigned r = threadIdx.x + QT * i;
             X[i][q] = (r < rows && q < kb) ? x[r] : 0.0;
         }
     }
+}
+
+// Applies the panel before (its NB columns at k0 - NB, T in T) to the panel in X, and to its rows
+// k0 - NB..k0-1 in memory: P = V^T C, W = T^T P, C -= V W.  The panel then goes on to its
+// factorisation from registers; through wy_update and memory a step of the 2400 x 1200 QR took
+// 72 us (at 2048 to 1537 rows), now 60.
+template <int RPT>
+__device__ __forceinline__ void panel_update(double *__restrict__ a, int m, int lda, int k0, int kb,
+                                             const double *__restrict__ T, double (&X)[RPT][NB], QrShared &sh) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, ql = lane >> 2;
+    const unsigned rows = (unsigned)(m - k0);
+    const int p0 = k0 - NB, tr = t % NB, tc = t / NB;  // row and column of a 16 x 16 block, t < 256
+    double *top = a + (int64_t)(k0 + min(tc, kb - 1)) * lda + p0 + tr;
+    double c_top = 0.0;
+    if (t < NB * NB) {
+        c_top = *top;
+        const double v = a[(int64_t)(p0 + tc) * lda + p0 + tr];
+        sh.Ts[t / NB][t % NB] = T[t];
+        sh.W[tr][tc] = c_top;
+        sh.G[tr][tc] = tr < tc ? 0.0 : (tr == tc ? 1.0 : v);  // the unit lower triangle of V
+    }
+    auto load_v = [&](double (&v)[RPT], int j) {
+        const double *x = a + (int64_t)(p0 + min(j, NB - 1)) * lda + k0;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const unsigned r = t + QT * i;
+            v[i] = r < rows ? x[r] : 0.0;
+        }
+    };
+    double v[RPT], next[RPT];
+    load_v(next, 0);
+#pragma unroll 1
+    for (int j = 0; j < NB; ++j) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) v[i] = next[i];
+        load_v(next, j + 1);
+        double d[NB];
+#pragma unroll
+        for (int q = 0; q < NB; ++q) d[q] = v[0] * X[0][q];
+#pragma unroll
+        for (int i = 1; i < RPT; ++i)
+#pragma unroll
+            for (int q = 0; q < NB; ++q) d[q] += v[i] * X[i][q];
+        const double part = wave_sums16(d, lane);
+        if ((lane & 3) == 0) sh.Pw[wave][j][ql] = part;
+    }
+    load_v(next, 0);
+    __syncthreads();
+    if (t < NB * NB) {  // P summed over the waves in order, then the rows above
+        double s = sh.Pw[0][tr][tc];
+#pragma unroll
+        for (int w = 1; w < QW; ++w) s += sh.Pw[w][tr][tc];
+#pragma unroll
+        for (int r = 0; r < NB; ++r) s += sh.G[r][tr] * sh.W[r][tc];
+        sh.Pw[0][tr][tc] = s;
+    }
+    __syncthreads();
+    if (t < NB * NB) {
+        double s = 0.0;
+        for (int l = 0; l <= tr; ++l) s += sh.Ts[l][tr] * sh.Pw[0][l][tc];
+        sh.W[tr][tc] = s;
+    }
+    __syncthreads();
+    if (t < NB * NB && tc < kb) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j) c_top -= sh.G[tr][j] * sh.W[j][tc];
+        *top = c_top;
+    }
+#pragma unroll 1
+    for (int j = 0; j < NB; ++j) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) v[i] = next[i];
+        load_v(next, j + 1);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const double w = sh.W[j][q];
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) X[i][q] -= v[i] * w;
+        }
+    }
+    __syncthreads();  // the factorisation writes G and Ts
+}
+
+// Factors the panel in X (panel_load) and forms T, as panel_qr_kernel does.  At step j the
+// registers hold the columns j, j+1, ..., 15, 0, ..., j-1, the last j of them reflectors already.
+template <int RPT>
+__device__ __forceinline__ void panel_registers(double *__restrict__ a, int m, int lda, int k0, int kb,
+                                                double (&X)[RPT][NB], double *__restrict__ tau, double *__restrict__ T,
+                                                QrShared &sh) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, ql = lane >> 2;
+    const unsigned rows = (unsigned)(m - k0);
 #pragma unroll 1
     for (int j = 0; j < NB; ++j) {
         double d[NB];
@@ -564,7 +653,9 @@ __global__ __launch_bounds__(QT) void qr_first_kernel(double *__restrict__ A, in
                                                       double *__restrict__ tau, int n, double *__restrict__ Tp) {
     __shared__ QrShared sh;
     const int b = blockIdx.x;
-    panel_registers<RPT>(A + (int64_t)b * stride, m, m, 0, kb, tau + (int64_t)b * n, Tp + (int64_t)b * NB * NB, sh);
+    double *a = A + (int64_t)b * stride, X[RPT][NB];
+    panel_load<RPT>(a, m, m, 0, kb, X);
+    panel_registers<RPT>(a, m, m, 0, kb, X, tau + (int64_t)b * n, Tp + (int64_t)b * NB * NB, sh);
 }
 
 // One step of the QR: the panel at k0 (factored, T in Tp) is applied to the columns after it,
@@ -576,10 +667,15 @@ __global__ __launch_bounds__(QT) void qr_step_kernel(double *__restrict__ A, int
     __shared__ QrShared sh;
     const int b = blockIdx.y, c = k0 + NB + (int)blockIdx.x * CT;
     double *a = A + (int64_t)b * stride;
-    wy_update(a, m, m, k0, NB, Tp + (int64_t)b * NB * NB, a, m, c, n, sh);
-    if (blockIdx.x != 0) return;  // uniform over the workgroup
-    __syncthreads();              // the updated columns are read back in the panel's layout
-    panel_registers<RPT>(a, m, m, c, min(NB, n - c), tau + (int64_t)b * n, Tnext + (int64_t)b * NB * NB, sh);
+    if (blockIdx.x != 0) {  // uniform over the workgroup
+        wy_update(a, m, m, k0, NB, Tp + (int64_t)b * NB * NB, a, m, c, n, sh);
+        return;
+    }
+    const int kb = min(NB, n - c);
+    double X[RPT][NB];
+    panel_load<RPT>(a, m, m, c, kb, X);
+    panel_update<RPT>(a, m, m, c, kb, Tp + (int64_t)b * NB * NB, X, sh);
+    panel_registers<RPT>(a, m, m, c, kb, X, tau + (int64_t)b * n, Tnext + (int64_t)b * NB * NB, sh);
 }
 
 // 16 columns of Q = H_0 H_1 ... [I; 0] in one workgroup's registers through all panels that reach
