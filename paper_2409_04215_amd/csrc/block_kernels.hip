@@ -16,6 +16,7 @@
 //  * Completion strengths (eqs. (al0), (lambda01), (lambda02)), recovery of
 //    phi / U (eqs. (vkal), (getU)), and setup assembly of
 //    S_L = S^(kk)(I - L) + L_r in FP64 (Section 3.3).
+#include "device_math.h"
 #include "mfs_internal.h"
 
 namespace mfs {
@@ -307,8 +308,7 @@ __global__ void gemm_reduce_kernel(const int32_t *__restrict__ col_group, const 
     const int M = groups[col_group[col]].M;
     const int m = blockIdx.y * blockDim.x + threadIdx.x;
     if (m >= M) return;
-    T s = 0;
-    for (int sp = 0; sp < n_split; ++sp) s += partial[sp * part_split_stride + (int64_t)col * part_col_stride + m];
+    const T s = strided_sum(partial + (int64_t)col * part_col_stride + m, part_split_stride, n_split);
     C[c_col_off[col] + m] = s;
 }
 
@@ -431,9 +431,7 @@ __global__ __launch_bounds__(256) void project_kernel(BodyView bv, const T *__re
     const T *pb = n_slices > 1 ? part + (int64_t)col_of_body[b] * col_stride : nullptr;
     auto val = [&](int64_t j) -> double {
         if (n_slices <= 1) return (double)lam[off + j];
-        T s = T(0);
-        for (int sp = 0; sp < n_slices; ++sp) s += pb[sp * split_stride + j];
-        return (double)s;
+        return (double)strided_sum(pb + j, split_stride, n_slices);
     };
     // the projection reads every value twice; the first pass keeps them here (each
     // thread reads back only its own entries)

@@ -34,4 +34,20 @@ __device__ __forceinline__ void rsq_cluster_end() {
     __builtin_amdgcn_s_setprio(0);
 }
 
+// p[0] + p[stride] + ... (n values) in order, their loads issued eight at a time: a loop of n dependent
+// loads and adds took 14 us of a launch for 14 split slices, 5 us so.
+template <class T>
+__device__ __forceinline__ T strided_sum(const T *__restrict__ p, int64_t stride, int n) {
+    T s = T(0);
+    for (int k = 0; k < n; k += 8) {
+        T v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = p[min(k + q, n - 1) * stride];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (k + q < n) s += v[q];
+    }
+    return s;
+}
+
 }  // namespace mfs

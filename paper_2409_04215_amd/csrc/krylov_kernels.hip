@@ -13,7 +13,8 @@ namespace {
 constexpr int DOT_GROUP = 8;
 
 // out[i] = sum_{n in chunk} V[i][n] w[n], i < nvec (one workgroup of 256 threads per chunk;
-// thread t visits n = begin + t, begin + t + 256, ...)
+// thread t visits n = begin + t, begin + t + 256, ...).  These kernels are latency: a group's
+// loads go out together, the last group's past nvec repeating its last vector.
 __device__ __forceinline__ void chunk_dots(const VecChunk ch, const double *V, int64_t ldv, int nvec,
                                            const double *w, double *__restrict__ out, double (*sh)[DOT_GROUP]) {
     const int tid = threadIdx.x;
@@ -24,9 +25,11 @@ __device__ __forceinline__ void chunk_dots(const VecChunk ch, const double *V, i
         const int ni = min(DOT_GROUP, nvec - i0);
         for (int64_t n = ch.begin + tid; n < ch.end; n += 256) {
             const double wn = w[n];
+            double v[DOT_GROUP];
 #pragma unroll
-            for (int q = 0; q < DOT_GROUP; ++q)
-                if (q < ni) acc[q] += V[(int64_t)(i0 + q) * ldv + n] * wn;
+            for (int q = 0; q < DOT_GROUP; ++q) v[q] = V[(int64_t)(i0 + min(q, ni - 1)) * ldv + n];
+#pragma unroll
+            for (int q = 0; q < DOT_GROUP; ++q) acc[q] += v[q] * wn;
         }
 #pragma unroll
         for (int q = 0; q < DOT_GROUP; ++q) {
@@ -47,15 +50,14 @@ __device__ __forceinline__ void chunk_dots(const VecChunk ch, const double *V, i
 __device__ __forceinline__ double combine(const double *__restrict__ V, int64_t ldv, int nvec,
                                           const double *__restrict__ cf, int64_t n) {
     double acc = 0.0;
-    int i = 0;
-    for (; i + DOT_GROUP <= nvec; i += DOT_GROUP) {
+    for (int i = 0; i < nvec; i += DOT_GROUP) {
         double v[DOT_GROUP];
 #pragma unroll
-        for (int q = 0; q < DOT_GROUP; ++q) v[q] = V[(int64_t)(i + q) * ldv + n];
+        for (int q = 0; q < DOT_GROUP; ++q) v[q] = V[(int64_t)min(i + q, nvec - 1) * ldv + n];
 #pragma unroll
-        for (int q = 0; q < DOT_GROUP; ++q) acc += v[q] * cf[i + q];
+        for (int q = 0; q < DOT_GROUP; ++q)
+            if (i + q < nvec) acc += v[q] * cf[i + q];
     }
-    for (; i < nvec; ++i) acc += V[(int64_t)i * ldv + n] * cf[i];
     return acc;
 }
 

@@ -193,8 +193,7 @@ __global__ void reduce3_kernel(int64_t n, const double *__restrict__ partial, in
                                double *__restrict__ out, int accumulate) {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= n) return;
-    double s = 0.0;
-    for (int k = 0; k < n_split; ++k) s += partial[k * stride + v];
+    double s = strided_sum(partial + v, stride, n_split);
     if (accumulate) s += out[v];
     out[v] = s;
 }
