@@ -49,6 +49,7 @@ namespace {
 constexpr int BLOCK = 256;
 constexpr int WAVES = BLOCK / 64;
 constexpr int FLUSH = 64;
+constexpr int STAGED_ITEMS = 1024;
 
 // Adds the FP64 accumulators of waves 1..WAVES-1 into wave 0's, in wave order.
 // lds holds (WAVES-1) * NV * 64 doubles.  Every thread of the workgroup must
@@ -336,7 +337,11 @@ __device__ __forceinline__ double far_total(FarSums &fs, uint4v *frag) {
 // ---------------------------------------------------------------------------
 // Mixed precision, Stokes / Laplace (one kernel; item.kind is wave-uniform)
 // ---------------------------------------------------------------------------
-template <int TPL>
+// STAGED: Stokes sources through LDS instead of scalar loads.  A launch with few waves per SIMD waits
+// for every scalar load (300 ns per four sources), one with many hides it and is faster without the
+// LDS reads: up to STAGED_ITEMS items, four waves per SIMD (6 bodies of 400 x 800, 450 items, in a
+// matvec of 48.4 us: 44.9; 3 of 1000 x 150 38.2: 28.6; beyond, 16 bodies of 400 x 800 72.4: 75.7).
+template <int TPL, bool STAGED>
 __device__ __forceinline__ void mixed_item(const KernelArgs &a, const P2PItem it, const float4 *__restrict__ trg_off,
                                            const SrcS32 *__restrict__ srcS, const SrcL32 *__restrict__ srcL,
                                            double *lds, float4 *stage) {
@@ -393,15 +398,24 @@ __device__ __forceinline__ void mixed_item(const KernelArgs &a, const P2PItem it
                 float p[TPL][3];
 #pragma unroll
                 for (int t = 0; t < TPL; ++t) p[t][0] = p[t][1] = p[t][2] = 0.f;
-                // four sources per 128-byte scalar load (s_load_dwordx16 pairs), then the tail
                 const SrcS32 *__restrict__ ps = srcS + jb;
                 const int n = je - jb;
                 int k = 0;
-                for (; k + 4 <= n; k += 4) {
-                    const Src4 q = *reinterpret_cast<const Src4 *>(ps + k);
-                    stokes_pairs<TPL, 4>(xr, q.s, p);
+                if constexpr (STAGED) {  // one coalesced load per run, as for Laplace below
+                    SrcS32 *slot = reinterpret_cast<SrcS32 *>(stage) + 64 * wv;
+                    if (lane < n) slot[lane] = ps[lane];
+                    wave_lds_order();
+                    for (; k + 4 <= n; k += 4) stokes_pairs<TPL, 4>(xr, slot + k, p);
+                    for (; k < n; ++k) stokes_pairs<TPL, 1>(xr, slot + k, p);
+                    __builtin_amdgcn_wave_barrier();  // the next run's stores follow this run's reads
+                } else {
+                    // four sources per 128-byte scalar load (s_load_dwordx16 pairs), then the tail
+                    for (; k + 4 <= n; k += 4) {
+                        const Src4 q = *reinterpret_cast<const Src4 *>(ps + k);
+                        stokes_pairs<TPL, 4>(xr, q.s, p);
+                    }
+                    for (; k < n; ++k) stokes_pairs<TPL, 1>(xr, ps + k, p);
                 }
-                for (; k < n; ++k) stokes_pairs<TPL, 1>(xr, ps + k, p);
 #pragma unroll
                 for (int t = 0; t < TPL; ++t) {
                     acc[t][0] += use[t] ? (double)p[t][0] : 0.0;
@@ -748,14 +762,14 @@ const SrcL64 *__restrict__ ps = srcL + j0;
 // One work item per workgroup, or (persistent mode) a fixed grid whose
 // workgroups claim items from a counter until the list is exhausted; every
 // workgroup ends with the claim that runs past the end, so the grid drains.
-template <int TPL>
+template <int TPL, bool STAGED>
 __global__ __launch_bounds__(BLOCK) void p2p_mixed_kernel(KernelArgs a, const float4 *__restrict__ trg_off,
                                                           const SrcS32 *__restrict__ srcS,
                                                           const SrcL32 *__restrict__ srcL) {
     __shared__ double lds[(WAVES - 1) * 3 * TPL * 64];
-    __shared__ float4 stage[WAVES * 64];
+    __shared__ float4 stage[WAVES * 64 * (STAGED ? 2 : 1)];
     if (!a.queue) {
-        mixed_item<TPL>(a, a.items[blockIdx.x], trg_off, srcS, srcL, lds, stage);
+        mixed_item<TPL, STAGED>(a, a.items[blockIdx.x], trg_off, srcS, srcL, lds, stage);
         return;
     }
     __shared__ int slot;
@@ -765,7 +779,7 @@ __global__ __launch_bounds__(BLOCK) void p2p_mixed_kernel(KernelArgs a, const fl
         __syncthreads();
         const int k = slot;
         if (k >= a.n_items) break;
-        mixed_item<TPL>(a, a.items[k], trg_off, srcS, srcL, lds, stage);
+        mixed_item<TPL, STAGED>(a, a.items[k], trg_off, srcS, srcL, lds, stage);
     }
 }
 
@@ -970,13 +984,16 @@ int launch_p2p(const P2PItems &pp, const P2PLaunch &L, hipStream_t s) {
         if (pp.wide)
             p2p_wide_kernel<<<grid, 64 * WIDE, 0, s>>>(a, RawPoints{L.raw_trg, L.raw_src, L.raw_str});
         else if (pp.tpl == 2)
-            p2p_mixed_kernel<2><<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcS32 *)L.srcS,
-                                                       (const SrcL32 *)L.srcL);
+            p2p_mixed_kernel<2, false><<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcS32 *)L.srcS,
+                                                              (const SrcL32 *)L.srcL);
         else if (pp.far)
             p2p_far_kernel<<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcL32 *)L.srcL);
+        else if (pp.n_items <= STAGED_ITEMS)
+            p2p_mixed_kernel<1, true><<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcS32 *)L.srcS,
+                                                             (const SrcL32 *)L.srcL);
         else
-            p2p_mixed_kernel<1><<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcS32 *)L.srcS,
-                                                       (const SrcL32 *)L.srcL);
+            p2p_mixed_kernel<1, false><<<grid, BLOCK, 0, s>>>(a, (const float4 *)L.trg_off, (const SrcS32 *)L.srcS,
+                                                              (const SrcL32 *)L.srcL);
     } else {
         if (pp.tpl == 2)
             p2p_f64_kernel<2><<<grid, BLOCK, 0, s>>>(a, (const double4 *)L.trg_off, (const SrcS64 *)L.srcS,

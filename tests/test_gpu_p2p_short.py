@@ -82,3 +82,23 @@ def test_output_in_place_of_the_strengths(kind):
     f(*geo, _dev(X), _dev(Y), buf, prec=mfs.MIXED, out=buf)
     # both errors are those of FP32 sums of the same terms
     assert rel_inf(buf.cpu().numpy(), apart) <= 1e-6
+
+
+@pytest.mark.parametrize("skip", [True, False])
+@pytest.mark.parametrize("n_src", [1, 3, 255, 256, 257, 300])
+@pytest.mark.parametrize("bodies,n_trg", [(3, 5483), (5, 3290)])
+def test_stokes_sources_through_lds(bodies, n_trg, n_src, skip):
+    """258 blocks of 64 targets: 774 work items take their sources through LDS, 1290 by scalar loads; quarters of a
+    body of one source, of none, and on both sides of the run of 64."""
+    from paper_2409_04215_amd import mfs
+    geo, X, tb, Y, sb, rg = _points((bodies,), (n_trg,), (n_src,), 45)
+    s = rg.standard_normal((len(Y), 3))
+    got = mfs.p2p_stokes(*geo, _dev(X), _dev(Y), _dev(s), flags=mfs.SKIP_SAME_BODY if skip else 0,
+                         prec=mfs.MIXED).cpu().numpy()
+    ref_pts = M.ref_first_source(bodies, sb, Y, tb, X)
+    rows = np.unique(np.concatenate([rg.integers(0, len(X), 200), [0, len(X) - 1]]))
+    model = {dt: M.pair_sum(O.STOKES, X[rows], tb[rows], Y, sb, s, ref_pts, skip, dt=dt) for dt in (np.float32, np.float64)}
+    bar = M.bar(rel_inf(model[np.float32], model[np.float64]), 6e-8)
+    e = rel_inf(got[rows], model[np.float64])
+    print(f"bodies={bodies} n_src={n_src} skip={skip} err={e:.2e} bar={bar:.2e}")
+    assert e <= bar
