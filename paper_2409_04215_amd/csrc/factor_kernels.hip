@@ -397,7 +397,6 @@ __device__ __forceinline__ void panel_update(double *__restrict__ a, int m, int 
         const double part = wave_sums16(d, lane);
         if ((lane & 3) == 0) sh.Pw[wave][j][ql] = part;
     }
-    load_v(next, 0);
     __syncthreads();
     if (t < NB * NB) {  // P summed over the waves in order, then the rows above
         double s = sh.Pw[0][tr][tc];
@@ -415,20 +414,23 @@ __device__ __forceinline__ void panel_update(double *__restrict__ a, int m, int 
     }
     __syncthreads();
     if (t < NB * NB && tc < kb) {
+        double o = 0.0;
 #pragma unroll
-        for (int j = 0; j < NB; ++j) c_top -= sh.G[tr][j] * sh.W[j][tc];
-        *top = c_top;
+        for (int j = 0; j < NB; ++j) o += sh.G[tr][j] * sh.W[j][tc];
+        *top = c_top - o;
     }
 #pragma unroll 1
-    for (int j = 0; j < NB; ++j) {
+    for (int j = 0; j < NB; j += 4) {  // four columns of V at a time: X is rounded four times
+        double u[4][RPT];
 #pragma unroll
-        for (int i = 0; i < RPT; ++i) v[i] = next[i];
-        load_v(next, j + 1);
+        for (int e = 0; e < 4; ++e) load_v(u[e], j + e);
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
-            const double w = sh.W[j][q];
+            double w[4];
 #pragma unroll
-            for (int i = 0; i < RPT; ++i) X[i][q] -= v[i] * w;
+            for (int e = 0; e < 4; ++e) w[e] = sh.W[j + e][q];
+#pragma unroll
+            for (int i = 0; i < RPT; ++i) X[i][q] -= u[0][i] * w[0] + u[1][i] * w[1] + u[2][i] * w[2] + u[3][i] * w[3];
         }
     }
     __syncthreads();  // the factorisation writes G and Ts
@@ -748,10 +750,10 @@ __global__ __launch_bounds__(QT) void q_kernel(const double *__restrict__ A, int
             sh.Pw[0][i][j] = s;
         }
         __syncthreads();
-        if (t < NB * CT) {  // -W = -T P
+        if (t < NB * CT) {  // W = T P
             const int i = t / CT, j = t % CT;
             double s = 0.0;
-            for (int l = i; l < NB; ++l) s -= sh.Ts[i][l] * sh.Pw[0][l][j];
+            for (int l = i; l < NB; ++l) s += sh.Ts[i][l] * sh.Pw[0][l][j];
             sh.W[i][j] = s;
         }
         __syncthreads();
@@ -776,13 +778,16 @@ __global__ __launch_bounds__(QT) void q_kernel(const double *__restrict__ A, int
             for (int i = 0; i < GR; ++i) {
                 const int bl = wave + QW * (g + i);
                 if (bl < p) continue;
+                doublex4 o = {0.0, 0.0, 0.0, 0.0};  // the product first: C is rounded once per panel
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int k = 4 * u + q;
                     double y = k < kb ? x[i][u] : 0.0;
                     if (bl == p) y = (rho < k || k >= kb) ? 0.0 : (rho == k ? 1.0 : y);
-                    C[g + i] = __builtin_amdgcn_mfma_f64_16x16x4f64(y, wv[u], C[g + i], 0, 0, 0);
+                    o = __builtin_amdgcn_mfma_f64_16x16x4f64(y, wv[u], o, 0, 0, 0);
                 }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) C[g + i][u] -= o[u];
             }
         }
     }
