@@ -627,7 +627,9 @@ struct mfs_plan_s {
         }
     } far_fwd, far_tr;
     // factors
-    DevBuf A32, A64;
+    DevBuf A64;        // FP64 factors, then the FP32 ones (one allocation: a large free takes 0.3 ms)
+    int64_t pool = 0;  // values of each
+    float *a32() const { return reinterpret_cast<float *>(A64.as<double>() + pool); }
     std::vector<Factor> factors;
     DevBuf d_col_gam, d_col_lam, d_col_of_body;
     // grouped GEMMs: forward U^T then W; transposed W^T then U
@@ -906,12 +908,13 @@ int build_gemm_tables(mfs_plan p, hipStream_t s) {
 // strided-batched SVD (in chunks that keep the scratch under ~4 GB).
 int factor_shapes(mfs_plan p, const mfs_plan_desc *d, const std::vector<int64_t> &shape_src_off,
                   const std::vector<int64_t> &shape_trg_off, hipStream_t s) {
-    rocblas_handle h;
-    if (rocblas_create_handle(&h) != rocblas_status_success) return fail(MFS_EHIP, "rocblas_create_handle failed");
+    const bool qr = p->factorization == MFS_FACTOR_QR;
+    rocblas_handle h = nullptr;  // for the SVD; its workspace takes 0.8 ms to allocate and free
+    if (!qr && rocblas_create_handle(&h) != rocblas_status_success) return fail(MFS_EHIP, "rocblas_create_handle failed");
     std::unique_ptr<rocblas_handle, void (*)(rocblas_handle *)> guard(&h, [](rocblas_handle *hh) {
-        rocblas_destroy_handle(*hh);
+        if (*hh) rocblas_destroy_handle(*hh);
     });
-    rocblas_set_stream(h, s);
+    if (h) rocblas_set_stream(h, s);
     // pool layout
     int64_t pool = 0;
     for (auto &F : p->factors) {
@@ -924,8 +927,9 @@ int factor_shapes(mfs_plan p, const mfs_plan_desc *d, const std::vector<int64_t>
         F.u_off = pool;
         pool += (int64_t)F.dM * F.dN;
     }
-    MFS_TRY(p->A64.reserve(std::max<int64_t>(1, pool) * sizeof(double)));
-    MFS_TRY(p->A32.reserve(std::max<int64_t>(1, pool) * sizeof(float)));
+    pool = std::max<int64_t>(32, (pool + 31) / 32 * 32);  // the FP32 part on a 256-byte boundary
+    MFS_TRY(p->A64.reserve(pool * (sizeof(double) + sizeof(float))));
+    p->pool = pool;
     // batches of equal (m, n)
     std::vector<std::vector<int>> batches;
     {
@@ -945,14 +949,13 @@ int factor_shapes(mfs_plan p, const mfs_plan_desc *d, const std::vector<int64_t>
             batches.back().push_back(keyed[i].second);
         }
     }
-    DevBuf SL, Ub, Vb, Sv, E, info, work, pts, gi, inv, tau;
+    DevBuf mats, Sv, E, info, work, pts, gi, inv, tau;
     for (auto &bt : batches) {
         const int B = (int)bt.size();
         const int m = p->factors[bt[0]].dM, n = p->factors[bt[0]].dN;
         const int64_t smn = (int64_t)m * n, snn = (int64_t)n * n;
-        MFS_TRY(SL.reserve((size_t)B * smn * sizeof(double)));
-        MFS_TRY(Ub.reserve((size_t)B * smn * sizeof(double)));
-        MFS_TRY(Vb.reserve((size_t)B * snn * sizeof(double)));
+        MFS_TRY(mats.reserve((size_t)B * (2 * smn + snn) * sizeof(double)));  // a large free takes 0.3 ms
+        double *SL = mats.as<double>(), *Ub = SL + B * smn, *Vb = Ub + B * smn;
         MFS_TRY(Sv.reserve((size_t)B * n * sizeof(double)));
         MFS_TRY(E.reserve((size_t)B * n * sizeof(double)));
         MFS_TRY(info.reserve((size_t)B * sizeof(rocblas_int)));
@@ -983,26 +986,26 @@ int factor_shapes(mfs_plan p, const mfs_plan_desc *d, const std::vector<int64_t>
             const int N = d->shape_n_src[F.shape], M = d->shape_n_trg[F.shape];
             const double *P = pts.as<double>() + pts_off[q];
             MFS_TRY(launch_assemble_SL(F.kind, M, N, P, P + 3 * (size_t)M, gi.as<double>() + 36 * q, p->mu,
-                                       p->formulation == MFS_RESISTANCE, SL.as<double>() + q * smn,
+                                       p->formulation == MFS_RESISTANCE, SL + q * smn,
                                        work.as<double>(), s));
         }
-        if (p->factorization == MFS_FACTOR_QR) {
+        if (qr) {
             // S_L = Q R (library QR): U^T <- Q^T, U <- Q, W <- R^-1, W^T <- R^-T
             MFS_TRY(tau.reserve(qr_scratch_doubles(B, n) * sizeof(double)));
-            MFS_TRY(qr_inverse_batched(B, SL.as<double>(), m, n, smn, Ub.as<double>(), smn, Vb.as<double>(), snn,
+            MFS_TRY(qr_inverse_batched(B, SL, m, n, smn, Ub, smn, Vb, snn,
                                        tau.as<double>(), Sv.as<double>(), s));
             std::vector<double> rat(B);
             MFS_HIP_TRY(hipMemcpyAsync(rat.data(), Sv.ptr, B * sizeof(double), hipMemcpyDeviceToHost, s));
             MFS_HIP_TRY(hipStreamSynchronize(s));
             double *A64 = p->A64.as<double>();
-            float *A32 = p->A32.as<float>();
+            float *A32 = p->a32();
             for (int q = 0; q < B; ++q) {
                 Factor &F = p->factors[bt[q]];
                 F.ratio = std::isfinite(rat[q]) ? rat[q] : 0.0;
                 p->min_ratio = std::min(p->min_ratio, F.ratio);
                 if (!(F.ratio > 1e-14))
                     return fail(MFS_ENUMERIC, "QR: 1/(|R|_F |R^-1|_F) = " + std::to_string(F.ratio) + " <= 1e-14");
-                const double *Q = Ub.as<double>() + q * smn, *X = Vb.as<double>() + q * snn;
+                const double *Q = Ub + q * smn, *X = Vb + q * snn;
                 MFS_TRY(launch_make_factor(n, m, Q, m, false, nullptr, nullptr, A64 + F.ut_off, A32 + F.ut_off, s));
                 MFS_TRY(launch_make_factor(m, n, Q, m, true, nullptr, nullptr, A64 + F.u_off, A32 + F.u_off, s));
                 // X column-major (ld n): W[r][c] = X[c n + r], W^T[r][c] = X[r n + c]
@@ -1013,8 +1016,8 @@ int factor_shapes(mfs_plan p, const mfs_plan_desc *d, const std::vector<int64_t>
             continue;
         }
         rocblas_status st = rocsolver_dgesvd_strided_batched(
-            h, rocblas_svect_singular, rocblas_svect_singular, m, n, SL.as<double>(), m, smn, Sv.as<double>(), n,
-            Ub.as<double>(), m, smn, Vb.as<double>(), n, snn, E.as<double>(), n, rocblas_outofplace,
+            h, rocblas_svect_singular, rocblas_svect_singular, m, n, SL, m, smn, Sv.as<double>(), n,
+            Ub, m, smn, Vb, n, snn, E.as<double>(), n, rocblas_outofplace,
             info.as<rocblas_int>(), B);
         if (st != rocblas_status_success) return fail(MFS_EHIP, "rocsolver_dgesvd_strided_batched failed");
         std::vector<double> sv((size_t)B * n);
@@ -1035,10 +1038,10 @@ int factor_shapes(mfs_plan p, const mfs_plan_desc *d, const std::vector<int64_t>
         }
         MFS_TRY(upload_vec(inv, hinv, s));
         double *A64 = p->A64.as<double>();
-        float *A32 = p->A32.as<float>();
+        float *A32 = p->a32();
         for (int q = 0; q < B; ++q) {
             const Factor &F = p->factors[bt[q]];
-            const double *U = Ub.as<double>() + q * smn, *V = Vb.as<double>() + q * snn;
+            const double *U = Ub + q * smn, *V = Vb + q * snn;
             const double *iv = inv.as<double>() + (size_t)q * n;
             // U^T (n x m): row r = column r of U (column-major, ld m)
             MFS_TRY(launch_make_factor(n, m, U, m, false, nullptr, nullptr, A64 + F.ut_off, A32 + F.ut_off, s));
@@ -1626,7 +1629,7 @@ int precond_fwd(mfs_plan p, const double *in, int prec, bool project, double *ou
     sl.col_of_body = p->d_col_of_body.as<int32_t>();
     if (f32) {
         MFS_TRY(launch_rotate_in(bv, in, p->ws_g32.ptr, true, false, s));
-        MFS_TRY(launch_gemm_f32(p->gm[0].L, p->A32.as<float>(), p->ws_g32.as<float>(), p->d_col_gam.as<int64_t>(),
+        MFS_TRY(launch_gemm_f32(p->gm[0].L, p->a32(), p->ws_g32.as<float>(), p->d_col_gam.as<int64_t>(),
                                 p->ws_l32a.as<float>(), p->d_col_lam.as<int64_t>(), p->gpart32.as<float>(), s));
         if (p->factorization == MFS_FACTOR_QR) {
             MFS_TRY(launch_cast(p->n_lambda, p->ws_l32a.ptr, true, p->ws_l64a.ptr, s));
@@ -1636,7 +1639,7 @@ int precond_fwd(mfs_plan p, const double *in, int prec, bool project, double *ou
             sl.part = p->gpart64.ptr;
             f32 = false;  // lambda in FP64
         } else {
-            MFS_TRY(launch_gemm_f32(G2, p->A32.as<float>(), p->ws_l32a.as<float>(), p->d_col_lam.as<int64_t>(),
+            MFS_TRY(launch_gemm_f32(G2, p->a32(), p->ws_l32a.as<float>(), p->d_col_lam.as<int64_t>(),
                                     p->ws_l32b.as<float>(), p->d_col_lam.as<int64_t>(), p->gpart32.as<float>(), s,
                                     false));
             sl.part = p->gpart32.ptr;
@@ -1676,11 +1679,11 @@ int precond_tr(mfs_plan p, const double *in, int prec, bool project, double *out
             MFS_TRY(launch_cast(p->n_lambda, p->ws_l64b.ptr, false, p->ws_l32b.ptr, s));
         } else {
             MFS_TRY(launch_rotate_in(bv, src, p->ws_l32a.ptr, true, true, s));
-            MFS_TRY(launch_gemm_f32(p->gm[2].L, p->A32.as<float>(), p->ws_l32a.as<float>(),
+            MFS_TRY(launch_gemm_f32(p->gm[2].L, p->a32(), p->ws_l32a.as<float>(),
                                     p->d_col_lam.as<int64_t>(), p->ws_l32b.as<float>(), p->d_col_lam.as<int64_t>(),
                                     p->gpart32.as<float>(), s));
         }
-        MFS_TRY(launch_gemm_f32(p->gm[3].L, p->A32.as<float>(), p->ws_l32b.as<float>(), p->d_col_lam.as<int64_t>(),
+        MFS_TRY(launch_gemm_f32(p->gm[3].L, p->a32(), p->ws_l32b.as<float>(), p->d_col_lam.as<int64_t>(),
                                 p->ws_g32.as<float>(), p->d_col_gam.as<int64_t>(), p->gpart32.as<float>(), s));
         return launch_rotate_out(bv, p->ws_g32.ptr, true, out, false, s);
     }
