@@ -21,7 +21,8 @@
 // FP64-accumulation precision exactly as there.
 // The transposed orientation gives dPhi/ds_j too (the velocity sum over the pairs
 // it has in hand): the three gradients of 60 Stokes bodies of 400 sources and 800
-// targets 1735 -> 1532 us, where a sum of its own walked the pairs a third time.
+// targets 1735 -> 1532 us, where a sum of its own walked the pairs a third time
+// (now 1405 us).
 #include "pair_math.h"
 
 namespace mfs {
@@ -30,7 +31,11 @@ namespace {
 
 constexpr int BLOCK = 256;
 constexpr int WAVES = BLOCK / 64;
-constexpr int FLUSH = 32;  // three FP32 sums and the coefficient of w per run: shorter runs than the velocity sums
+// Sources per FP32 run.  Each adds two terms to the sums, so the runs are shorter than the velocity
+// sums' 64: at 16 the three gradients of 60 bodies err by 1.43e-7, 2.33e-7 and 2.38e-7 (1405 us), at
+// 32 by 1.80e-7, 2.60e-7 and 2.66e-7 (1377 us); with a term's sum added once per source and runs of
+// 32 it was 1.48e-7, 2.42e-7 and 2.48e-7 (1519 us).
+constexpr int FLUSH = 16;
 
 struct GradArgs {
     const P2PItem *items;
@@ -45,6 +50,9 @@ struct GradArgs {
     int skip_same;
     int accumulate;
 };
+
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // U Stokes sources: with c = 1/r^3, the pair's gradient is
 //   c (-(w.s) - 3 (w.d)(s.d) / r^2) d + c (w.d) s + c (s.d) w.
@@ -75,8 +83,9 @@ __device__ __forceinline__ void stokes_grad(const R (&xr)[3], const R (&w)[3], c
         pw += e;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            p[c] += k * d[u][c] + a * s[u][c];
-            if (SUM) v[c] += e * d[u][c] + ri[u] * s[u][c];
+            // two FMAs each: added up as written, the two terms would cost a multiplication more
+            p[c] = fma_(k, d[u][c], fma_(a, s[u][c], p[c]));
+            if (SUM) v[c] = fma_(e, d[u][c], fma_(ri[u], s[u][c], v[c]));
         }
     }
 }
