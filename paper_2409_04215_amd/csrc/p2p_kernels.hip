@@ -186,7 +186,7 @@ struct KernelArgs {
 // own in the block and extreme scales take the VALU path.
 // Rate: a pair is v_rsq_f32 and one FMA on the VALU (5.2 ns per 64 pairs and SIMD in a bare
 // loop, 13.3 with the six operations of r^2), the MFMA (1.7 ns) runs beside them.
-// 250 bodies, 389 sources and 777 targets each: 3285 -> 2354 us (8.0e12 pairs/s).
+// 250 bodies, 389 sources and 777 targets each: 3285 -> 2297 us (8.2e12 pairs/s).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_head(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
 __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {  // both exact in bf16
@@ -299,26 +299,26 @@ __device__ __forceinline__ void far_body(const uint4v *__restrict__ tiles, const
 #pragma unroll
     for (int t = 0; t < 4; ++t) A[t] = __builtin_bit_cast(bf16x8, frag[64 * g + 16 * t + c16]);
     __builtin_amdgcn_wave_barrier();  // the next body's stores follow these reads
+    auto tile = [&](int k, auto add) {  // add(i, strength, 1 / r)
+        const bf16x8 Bk = __builtin_bit_cast(bf16x8, B);
+        const float q = str[far_source(k, nt, lane)];
+        B = (tiles + 64 * (int64_t)min(k + 1, nt - 1))[(unsigned)lane];  // uniform base, 32-bit lane offset
+        const float4v zero = {0.f, 0.f, 0.f, 0.f};
+        float4v r2[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) r2[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[t], Bk, zero, 0, 0, 0);
+        rsq_cluster_begin();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) r2[i / 4][i % 4] = __builtin_amdgcn_rsqf(r2[i / 4][i % 4]);
+        rsq_cluster_end();
+#pragma unroll
+        for (int i = 0; i < 16; ++i) add(i, q, r2[i / 4][i % 4]);
+    };
     for (int kr = 0; kr < nt; kr += FAR_RUN) {
-        const int kend = min(kr + FAR_RUN, nt);
         float part[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) part[i] = 0.f;
-        for (int k = kr; k < kend; ++k) {
-            const bf16x8 Bk = __builtin_bit_cast(bf16x8, B);
-            const float q = str[far_source(k, nt, lane)];
-            B = (tiles + 64 * (int64_t)min(k + 1, nt - 1))[(unsigned)lane];  // uniform base, 32-bit lane offset
-            const float4v zero = {0.f, 0.f, 0.f, 0.f};
-            float4v r2[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) r2[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[t], Bk, zero, 0, 0, 0);
-            rsq_cluster_begin();
-#pragma unroll
-            for (int i = 0; i < 16; ++i) r2[i / 4][i % 4] = __builtin_amdgcn_rsqf(r2[i / 4][i % 4]);
-            rsq_cluster_end();
-#pragma unroll
-            for (int i = 0; i < 16; ++i) part[i] = __builtin_fmaf(q, r2[i / 4][i % 4], part[i]);
-        }
+        tile(kr, [&](int i, float q, float ri) { part[i] = q * ri; });
+        for (int k = kr + 1; k < min(kr + FAR_RUN, nt); ++k)
+            tile(k, [&](int i, float q, float ri) { part[i] = __builtin_fmaf(q, ri, part[i]); });
 #pragma unroll
         for (int i = 0; i < 16; ++i) fs.run[i] += part[i];
     }
