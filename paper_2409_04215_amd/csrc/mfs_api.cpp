@@ -285,7 +285,7 @@ struct Workspace {
     std::vector<std::unique_ptr<Layout>> layouts;
     uint64_t clock = 0;
 };
-constexpr size_t kMaxLayouts = 8;
+constexpr size_t kMaxLayouts = 16;  // 8 structures, each with mixed pair sums and with everything else
 
 // one workspace per host thread and device
 Workspace &workspace() {

@@ -346,7 +346,7 @@ struct GivensState {
 int launch_givens_init(const GivensState &st, hipStream_t s);
 
 // Batched FP64 Householder QR of column-major m x n matrices A (leading dimension m, m >= n,
-// n <= 8192), factor_kernels.hip, blocked in panels of 32 columns (compact WY, trailing
+// n <= 8192), factor_kernels.hip, blocked in panels of 16 columns (compact WY, trailing
 // updates and the accumulation of Q on the FP64 matrix cores): A is overwritten by R (upper
 // triangle) and the reflectors, Q (m x n, leading dimension m) and X = R^-1 (n x n, leading
 // dimension n) are written, and ratio[b] = 1 / (||R||_F ||R^-1||_F).  scratch: device
