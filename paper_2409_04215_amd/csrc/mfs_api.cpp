@@ -382,14 +382,18 @@ int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_s
     std::vector<int32_t> kob(std::max<int64_t>(1, nb), kind);
     const int min_items = default_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, kind,
                                             kStandaloneMinItems);
+    // One walk or the other: their items differ (64 and 256 targets).  Where both rules hold, the two take the
+    // same time (us, wide and far: 32 bodies of 500 x 512 58 and 56, 199 of 84 x 82 72 and 73, 2 x 40 of
+    // 400 x 204 55 and 59; without either 72, 114, 75), so the one that needs no operands is taken.
+    const bool wide = variant == kind && mixed && use_wide_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, kind);
     std::vector<int32_t> tiles;
-    l->far = mixed && kind == MFS_LAPLACE && use_far_tiles(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, tiles);
+    l->far = !wide && mixed && kind == MFS_LAPLACE &&
+             use_far_tiles(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, tiles);
     if (l->far) {
         l->tiles_h.swap(tiles);
         l->n_tiles = l->tiles_h.back();
         MFS_TRY(upload_vec(l->tile_ptr, l->tiles_h, s));
     }
-    const bool wide = variant == kind && mixed && use_wide_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, kind);
     MFS_TRY(build_p2p_items(l->pp, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, out_ptr.data(), kob.data(), mu, 1,
                             wide ? 1 : min_items, s, l->far));
     l->pp.wide = wide;

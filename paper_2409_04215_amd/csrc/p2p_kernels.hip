@@ -953,6 +953,7 @@ P2PItems items_of(const P2PPlan &pp) {
 
 int launch_p2p(const P2PItems &pp, const P2PLaunch &L, hipStream_t s) {
     if (pp.n_items == 0) return MFS_OK;
+    if (pp.wide && pp.far) return fail(MFS_EINVAL, "pair sum: items of one walk given to another");
     KernelArgs a;
     a.items = pp.items;
     a.centre = L.centre;
