@@ -126,10 +126,12 @@ def _ptr(t: Optional[torch.Tensor]):
     return ctypes.c_void_p(t.data_ptr())
 
 
-def _result(flags, ptr, *shape, device):
-    """A new output of the points that ptr covers: the library writes every value, or adds to
-    zeros with ACCUMULATE; points past the structure's last one stay zero."""
-    new = torch.zeros if flags & ACCUMULATE or shape[0] != ptr[-1] else torch.empty
+def _result(flags, sys_ptr, ptr, *shape, device):
+    """A new output for the points of a standalone call: the library writes those of the bodies that
+    the systems use, the first sys_ptr[-1], or adds to zeros with ACCUMULATE; other points stay zero."""
+    used = sys_ptr[-1] if len(sys_ptr) else -1
+    whole = 0 <= used < len(ptr) and shape[0] == ptr[used]
+    new = torch.empty if whole and not flags & ACCUMULATE else torch.zeros
     return new(*shape, dtype=torch.float64, device=device)
 
 
@@ -155,7 +157,7 @@ def p2p_laplace(sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, src_xyz, src_
     """out_i = sum_j q_j / (4 pi |x_i - y_j|) over pairs of the same system (see mfs.h)."""
     keep = _geo(sys_body_ptr, body_trg_ptr, body_src_ptr)
     if out is None:
-        out = _result(flags, keep[1], trg_xyz.shape[0], device=trg_xyz.device)
+        out = _result(flags, keep[0], keep[1], trg_xyz.shape[0], device=trg_xyz.device)
     _check(lib().mfs_p2p_laplace(*keep[3], _ptr(trg_xyz), _ptr(src_xyz), _ptr(src_q), _ptr(out), flags, prec,
                                  _stream(stream)), "mfs_p2p_laplace")
     return out
@@ -166,7 +168,7 @@ def p2p_stokes(sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, src_xyz, src_f
     """out_i = sum_j G_stokeslet(x_i - y_j) f_j over pairs of the same system (see mfs.h)."""
     keep = _geo(sys_body_ptr, body_trg_ptr, body_src_ptr)
     if out is None:
-        out = _result(flags, keep[1], trg_xyz.shape[0], 3, device=trg_xyz.device)
+        out = _result(flags, keep[0], keep[1], trg_xyz.shape[0], 3, device=trg_xyz.device)
     _check(lib().mfs_p2p_stokes(*keep[3], _ptr(trg_xyz), _ptr(src_xyz), _ptr(src_f), _ptr(out), float(mu), flags,
                                 prec, _stream(stream)), "mfs_p2p_stokes")
     return out
@@ -178,7 +180,7 @@ def p2p_stokes_noalloc(sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, src_xy
     library (its scratch is a fixed per-GPU array; synchronous; see mfs.h)."""
     keep = _geo(sys_body_ptr, body_trg_ptr, body_src_ptr)
     if out is None:
-        out = _result(flags, keep[1], trg_xyz.shape[0], 3, device=trg_xyz.device)
+        out = _result(flags, keep[0], keep[1], trg_xyz.shape[0], 3, device=trg_xyz.device)
     _check(lib().mfs_p2p_stokes_noalloc(*keep[3], _ptr(trg_xyz), _ptr(src_xyz), _ptr(src_f), _ptr(out), float(mu),
                                         flags, prec, _stream(stream)), "mfs_p2p_stokes_noalloc")
     return out
@@ -189,7 +191,7 @@ def p2p_stokes_pressure(sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, src_x
     """p_i = (1/(8 pi)) sum_j Pi(x_i - y_j) . f_j (see mfs.h)."""
     keep = _geo(sys_body_ptr, body_trg_ptr, body_src_ptr)
     if out is None:
-        out = _result(flags, keep[1], trg_xyz.shape[0], device=trg_xyz.device)
+        out = _result(flags, keep[0], keep[1], trg_xyz.shape[0], device=trg_xyz.device)
     _check(lib().mfs_p2p_stokes_pressure(*keep[3], _ptr(trg_xyz), _ptr(src_xyz), _ptr(src_f), _ptr(out), flags,
                                          prec, _stream(stream)), "mfs_p2p_stokes_pressure")
     return out
@@ -200,7 +202,7 @@ def p2p_stokes_traction(sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, trg_n
     """sigma(x_i) . n_i of the Stokeslet sum (see mfs.h)."""
     keep = _geo(sys_body_ptr, body_trg_ptr, body_src_ptr)
     if out is None:
-        out = _result(flags, keep[1], trg_xyz.shape[0], 3, device=trg_xyz.device)
+        out = _result(flags, keep[0], keep[1], trg_xyz.shape[0], 3, device=trg_xyz.device)
     _check(lib().mfs_p2p_stokes_traction(*keep[3], _ptr(trg_xyz), _ptr(trg_normal), _ptr(src_xyz), _ptr(src_f),
                                          _ptr(out), flags, prec, _stream(stream)), "mfs_p2p_stokes_traction")
     return out
@@ -211,7 +213,7 @@ def p2p_laplace_gradient(sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, src_
     """grad u(x_i) of the Laplace sum (see mfs.h)."""
     keep = _geo(sys_body_ptr, body_trg_ptr, body_src_ptr)
     if out is None:
-        out = _result(flags, keep[1], trg_xyz.shape[0], 3, device=trg_xyz.device)
+        out = _result(flags, keep[0], keep[1], trg_xyz.shape[0], 3, device=trg_xyz.device)
     _check(lib().mfs_p2p_laplace_gradient(*keep[3], _ptr(trg_xyz), _ptr(src_xyz), _ptr(src_q), _ptr(out), flags,
                                           prec, _stream(stream)), "mfs_p2p_laplace_gradient")
     return out
@@ -221,9 +223,9 @@ def p2p_laplace_backward(sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, src_
                          want=("src", "trg_xyz", "src_xyz"), flags=SKIP_SAME_BODY, prec=MIXED, stream=None):
     keep = _geo(sys_body_ptr, body_trg_ptr, body_src_ptr)
     dev = trg_xyz.device
-    gq = _result(flags, keep[2], src_xyz.shape[0], device=dev) if "src" in want else None
-    gx = _result(flags, keep[1], trg_xyz.shape[0], 3, device=dev) if "trg_xyz" in want else None
-    gy = _result(flags, keep[2], src_xyz.shape[0], 3, device=dev) if "src_xyz" in want else None
+    gq = _result(flags, keep[0], keep[2], src_xyz.shape[0], device=dev) if "src" in want else None
+    gx = _result(flags, keep[0], keep[1], trg_xyz.shape[0], 3, device=dev) if "trg_xyz" in want else None
+    gy = _result(flags, keep[0], keep[2], src_xyz.shape[0], 3, device=dev) if "src_xyz" in want else None
     _check(lib().mfs_p2p_laplace_backward(*keep[3], _ptr(trg_xyz), _ptr(src_xyz), _ptr(src_q), _ptr(trg_w),
                                           _ptr(gq), _ptr(gx), _ptr(gy), flags, prec, _stream(stream)),
            "mfs_p2p_laplace_backward")
@@ -234,9 +236,9 @@ def p2p_stokes_backward(sys_body_ptr, body_trg_ptr, body_src_ptr, trg_xyz, src_x
                         want=("src", "trg_xyz", "src_xyz"), flags=SKIP_SAME_BODY, prec=MIXED, stream=None):
     keep = _geo(sys_body_ptr, body_trg_ptr, body_src_ptr)
     dev = trg_xyz.device
-    gf = _result(flags, keep[2], src_xyz.shape[0], 3, device=dev) if "src" in want else None
-    gx = _result(flags, keep[1], trg_xyz.shape[0], 3, device=dev) if "trg_xyz" in want else None
-    gy = _result(flags, keep[2], src_xyz.shape[0], 3, device=dev) if "src_xyz" in want else None
+    gf = _result(flags, keep[0], keep[2], src_xyz.shape[0], 3, device=dev) if "src" in want else None
+    gx = _result(flags, keep[0], keep[1], trg_xyz.shape[0], 3, device=dev) if "trg_xyz" in want else None
+    gy = _result(flags, keep[0], keep[2], src_xyz.shape[0], 3, device=dev) if "src_xyz" in want else None
     _check(lib().mfs_p2p_stokes_backward(*keep[3], _ptr(trg_xyz), _ptr(src_xyz), _ptr(src_f), _ptr(trg_w),
                                          _ptr(gf), _ptr(gx), _ptr(gy), float(mu), flags, prec, _stream(stream)),
            "mfs_p2p_stokes_backward")
