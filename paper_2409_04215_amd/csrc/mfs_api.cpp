@@ -179,7 +179,8 @@ int default_min_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t 
 // 532 for a batch of both), a system of at least
 // 32 bodies (below, most are near some of an item's targets) and 2.5e8 pairs (below, 256 targets
 // to an item leave the chip too few: 48 bodies of 200 x 400 took 66 us instead of 60, 32 of
-// 389 x 777 79 us instead of 86), whole tiles but for a quarter, and bodies that are one FP32 run.
+// 389 x 777 79 us instead of 86), whole tiles but for a quarter, and bodies of at most 1024 sources (their
+// strengths stay in LDS, 4 KB a wave).
 bool use_far_tiles(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                    const int64_t *body_src_ptr, const int32_t *kind_of_body, std::vector<int32_t> &tile_ptr) {
     int64_t most = 0, sources = 0, tiles = 0;
@@ -193,7 +194,7 @@ bool use_far_tiles(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *bo
         pairs += (double)(body_trg_ptr[b1] - body_trg_ptr[b0]) * (double)(body_src_ptr[b1] - body_src_ptr[b0]);
         for (int64_t b = b0; b < b1; ++b) {
             const int64_t n = body_src_ptr[b + 1] - body_src_ptr[b];
-            if (n > 1024) return false;  // FLUSH tiles, one FP32 run
+            if (n > 1024) return false;  // far_body holds that many strengths
             tile_ptr[b] = (int32_t)tiles;
             sources += n;
             tiles += (n + 15) / 16;

@@ -186,7 +186,7 @@ struct KernelArgs {
 // own in the block and extreme scales take the VALU path.
 // Rate: a pair is v_rsq_f32 and one FMA on the VALU (5.2 ns per 64 pairs and SIMD in a bare
 // loop, 13.3 with the six operations of r^2), the MFMA (1.7 ns) runs beside them.
-// 250 bodies, 389 sources and 777 targets each: 3285 -> 2297 us (8.2e12 pairs/s).
+// 250 bodies, 389 sources and 777 targets each: 3285 -> 2387 us (7.9e12 pairs/s).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_head(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
 __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {  // both exact in bf16
@@ -224,12 +224,10 @@ __device__ __forceinline__ uint4v pack_far_tile(const double (&y)[3], int lane) 
     return uint4v{BF16_ONES, BF16_ONES, bf16_pair(p[0], p[1]), bf16_pair(p[2], p[3])};
 }
 
-// Sums of one wave's far bodies.  run: targets 16 t + 4 (l/16) + r against the sources l%16 of the
-// tiles since the last flush; sum: the flushed total of target far_target(l).
+// Sums of one wave's far bodies, value i = 4 t + r: target 16 t + 4 (l/16) + r against the sources
+// that lane l has had.
 struct FarSums {
-    float run[16];
-    double sum;
-    int tiles;  // since the last flush
+    double sum[16];
 };
 
 template <int CTRL>
@@ -239,16 +237,10 @@ __device__ __forceinline__ double dpp_move(double x) {  // x of another lane of 
     return __hiloint2double(hi, lo);
 }
 
-// Adds run into the totals: the 16 values are summed over the row's 16 lanes in FP64, every
-// exchange halving what a lane carries, which leaves lane l value i = l%16.
-__device__ __forceinline__ void far_flush(FarSums &fs) {
+// The values summed over the row's 16 lanes, every exchange halving what a lane carries, which leaves
+// lane l value i = l%16.
+__device__ __forceinline__ double far_row_sum(double (&v)[16]) {
     const int lane = threadIdx.x & 63;
-    double v[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        v[i] = (double)fs.run[i];
-        fs.run[i] = 0.f;
-    }
 #pragma unroll
     for (int h = 8; h >= 1; h >>= 1) {
         const bool up = (lane & h) != 0;
@@ -264,25 +256,26 @@ __device__ __forceinline__ void far_flush(FarSums &fs) {
             v[i] = keep + got;
         }
     }
-    fs.sum += v[0];
-    fs.tiles = 0;
+    return v[0];
 }
 __device__ __forceinline__ int far_target(int lane) {  // value i = 4 t + r of row g: target 16 t + 4 g + r
     return 16 * ((lane & 15) >> 2) + 4 * (lane >> 4) + (lane & 3);
 }
 
 // All sources of one far body against the wave's 64 targets; x: this lane's target relative to
-// the body's centre, frag: 4 KB and str: 1024 floats of the wave's own.  The next
-// tile is fetched while this one is summed (250 bodies of 389 sources: 2336 us, two ahead 2411,
-// four 2729: registers).  FAR_RUN tiles make a sum of their own first (a tenth off the error of a
-// sum over ill-conditioned strengths, for one FMA in FAR_RUN).
-constexpr int FAR_RUN = 8;
+// the body's centre, frag: 4 KB and str: 1024 floats of the wave's own.  The next tile is fetched
+// while this one is summed (two ahead 3% slower, four 17%: registers).
+// A lane adds its FP32 sum to FP64 every FAR_RUN tiles and at the end of a body: four neighbouring
+// sources, where a run of the walk above has up to 64, because the bf16 r^2 errs from pair to pair.
+// Error against 64 bits over the walk without far tiles, of sums over pseudo-inverse strengths of
+// smooth data, aspects 2 and 3, 100 to 800 sources (24 suspensions each): 0.72 to 0.97 with runs of 4,
+// 0.85 to 1.10 with 8, 0.86 to 1.13 with 16, and 0.86 to 1.19 with an FP32 sum carried over 64 tiles.
+// 250 bodies of 389 sources: 2387, 2324, 2283 and 2298 us.
+constexpr int FAR_RUN = 4;
 __device__ __forceinline__ void far_body(const uint4v *__restrict__ tiles, const SrcL32 *__restrict__ src, int n,
                                          const double (&x)[3], uint4v *frag, float *str, FarSums &fs) {
     const int lane = threadIdx.x & 63, g = lane >> 4, c16 = lane & 15;
-    const int nt = (n + 15) / 16;  // at most FLUSH
-    if (fs.tiles + nt > FLUSH) far_flush(fs);
-    fs.tiles += nt;
+    const int nt = (n + 15) / 16;  // at most 64
     uint4v B = tiles[(unsigned)lane];
     for (int j = lane; j < 16 * nt; j += 64) str[j] = j < n ? src[j].w : 0.f;
 #pragma unroll
@@ -320,16 +313,15 @@ __device__ __forceinline__ void far_body(const uint4v *__restrict__ tiles, const
         for (int k = kr + 1; k < min(kr + FAR_RUN, nt); ++k)
             tile(k, [&](int i, float q, float ri) { part[i] = __builtin_fmaf(q, ri, part[i]); });
 #pragma unroll
-        for (int i = 0; i < 16; ++i) fs.run[i] += part[i];
+        for (int i = 0; i < 16; ++i) fs.sum[i] += (double)part[i];
     }
 }
 
 // The wave's far sums, lane l: target l
 __device__ __forceinline__ double far_total(FarSums &fs, uint4v *frag) {
-    far_flush(fs);
     const int lane = threadIdx.x & 63;
     double *tot = reinterpret_cast<double *>(frag);
-    tot[far_target(lane)] = fs.sum;
+    tot[far_target(lane)] = far_row_sum(fs.sum);
     wave_lds_order();
     return tot[lane];
 }
@@ -491,9 +483,7 @@ __device__ __forceinline__ void laplace_far_item(const KernelArgs &a, const P2PI
     double acc = 0.0;
     FarSums fs;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) fs.run[q] = 0.f;
-    fs.sum = 0.0;
-    fs.tiles = 0;
+    for (int q = 0; q < 16; ++q) fs.sum[q] = 0.0;
     for (int b = it.b0; active && b < it.b1; ++b) {
         const int s0 = a.src_ptr[b], s1 = a.src_ptr[b + 1];
         const bool use = !(a.skip_same && body == b);
@@ -509,8 +499,9 @@ __device__ __forceinline__ void laplace_far_item(const KernelArgs &a, const P2PI
         }
         const float xr[1][3] = {{xt.x + (float)(ct0 - a.centre[3 * b]), xt.y + (float)(ct1 - a.centre[3 * b + 1]),
                                  xt.z + (float)(ct2 - a.centre[3 * b + 2])}};
-        for (int jb = s0; jb < s1; jb += FLUSH) {
-            const int cnt = min(FLUSH, s1 - jb);
+        const int run = min(FLUSH, (s1 - s0 + WAVES - 1) / WAVES);  // no longer than a wave's of mixed_item
+        for (int jb = s0; jb < s1; jb += run) {
+            const int cnt = min(run, s1 - jb);
             float p[1] = {0.f};
             if (lane < cnt) slot[lane] = srcL[jb + lane];
             wave_lds_order();
