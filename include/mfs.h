@@ -387,10 +387,11 @@ int mfs_plan_last_solve(mfs_plan plan, int32_t *mixed_matvecs, int32_t *fp64_mat
  * launches only.  Ignored while timing is enabled.  mfs_plan_autotune: times
  * the matvec pair sum for candidate launch shapes (1 or 2 targets per lane x
  * 1024..16384 work items, which sets the source split x one workgroup per
- * item or a persistent grid of 2048 workgroups claiming items from a queue)
- * on `stream`, reps launches each, and keeps for the forward and transposed
- * sums the shape with the fewest source splits among those within 1.5% of the
- * fastest (timing noise; fewer splits write fewer FP64 slices), reporting it
+ * item or a persistent grid of 2048 workgroups claiming items from a queue, and
+ * the shape that the plan has) on `stream`, reps launches each, and keeps for
+ * the forward and transposed sums the shape with the fewest source splits among
+ * those within 1.5% of the fastest (timing noise; fewer splits write fewer FP64
+ * slices) and no slower than the plan's shape, reporting it
  * ([host] outputs, may be NULL; *best_tpl is negative for the persistent
  * grid).  Synchronous. */
 int mfs_plan_set_graph(mfs_plan plan, int32_t enable);

@@ -2365,56 +2365,62 @@ extern "C" int mfs_plan_autotune(mfs_plan p, int32_t prec, int32_t reps, int32_t
     hipEvent_t e0 = ev.e[0], e1 = ev.e[1];
     double best = 1e300;
     int btpl = p->tuned_tpl, bmi = p->tuned_min_items;
-    const int tpls[2] = {1, 2};
-    const int mis[5] = {1024, 2048, 4096, 8192, 16384};
-    bool bper = false;
-    int status = MFS_OK;
-    struct Cand { double ms; int n_split, tpl, mi, per; };
+    // the shapes listed and the plan's own, so that tuning never ends in a slower one
+    struct Shape { int tpl, mi, per; };
+    const Shape own{p->tuned_tpl, p->tuned_min_items, p->tuned_persistent ? 1 : 0};
+    std::vector<Shape> shapes;
+    for (int per = 0; per < 2; ++per)
+        for (int tpl = 1; tpl <= 2; ++tpl)
+            for (int mi = 1024; mi <= 16384; mi *= 2) shapes.push_back(Shape{tpl, mi, per});
+    size_t own_at = 0;
+    while (own_at < shapes.size() && (shapes[own_at].tpl != own.tpl || shapes[own_at].mi != own.mi || shapes[own_at].per != own.per))
+        ++own_at;
+    if (own_at == shapes.size()) shapes.push_back(own);
+    bool bper = own.per != 0;
+    struct Cand { double ms; int n_split; size_t n_items; Shape sh; };
     std::vector<Cand> timed;
-    for (int per = 0; per < 2 && status >= 0; ++per) {
-        for (int tpl : tpls) {
-            for (int mi : mis) {
-                P2PPlan cand;
-                status = build_p2p_items(cand, p->n_sys, p->sys_body_ptr.data(), trg_row.data(), src_row.data(),
-                                         p->gam_off.data(), p->kind.data(), p->mu, tpl, mi, s,
-                                         prec == MFS_MIXED && p->far_fwd.use && tpl == 1);
-                if (status < 0) break;
-                cand.persistent = per != 0;
-                const int64_t need = (cand.n_split > 1 ? cand.n_split : 1) * std::max<int64_t>(1, p->n_gamma);
-                if ((size_t)need * sizeof(double) > p->partial.bytes) {
-                    MFS_HIP_TRY(hipStreamSynchronize(s));
-                    status = grow_partial(p, need);
-                    if (status < 0) break;
-                }
-                P2PLaunch L = fwd_launch(p, prec);
-                L.skip_same = true;
-                L.out = p->ws_g64.as<double>();
-                status = launch_p2p(cand, L, s);  // warm-up
-                if (status < 0) break;
-                MFS_HIP_TRY(hipEventRecord(e0, s));
-                for (int r = 0; r < reps && status >= 0; ++r) status = launch_p2p(cand, L, s);
-                MFS_HIP_TRY(hipEventRecord(e1, s));
-                MFS_HIP_TRY(hipEventSynchronize(e1));
-                float ms = 0.f;
-                MFS_HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
-                timed.push_back(Cand{ms / reps, std::max(cand.n_split, 1), tpl, mi, per});
-            }
-            if (status < 0) break;
+    for (const Shape &sh : shapes) {
+        P2PPlan cand;
+        MFS_TRY(build_p2p_items(cand, p->n_sys, p->sys_body_ptr.data(), trg_row.data(), src_row.data(),
+                                p->gam_off.data(), p->kind.data(), p->mu, sh.tpl, sh.mi, s,
+                                prec == MFS_MIXED && p->far_fwd.use && sh.tpl == 1));
+        cand.persistent = sh.per != 0;
+        const int64_t need = (cand.n_split > 1 ? cand.n_split : 1) * std::max<int64_t>(1, p->n_gamma);
+        if ((size_t)need * sizeof(double) > p->partial.bytes) {
+            MFS_HIP_TRY(hipStreamSynchronize(s));
+            MFS_TRY(grow_partial(p, need));
         }
+        P2PLaunch L = fwd_launch(p, prec);
+        L.skip_same = true;
+        L.out = p->ws_g64.as<double>();
+        MFS_TRY(launch_p2p(cand, L, s));  // warm-up
+        MFS_HIP_TRY(hipEventRecord(e0, s));
+        for (int r = 0; r < reps; ++r) MFS_TRY(launch_p2p(cand, L, s));
+        MFS_HIP_TRY(hipEventRecord(e1, s));
+        MFS_HIP_TRY(hipEventSynchronize(e1));
+        float ms = 0.f;
+        MFS_HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+        timed.push_back(Cand{ms / reps, std::max(cand.n_split, 1), cand.items.size(), sh});
     }
-    if (status < 0) return status;
     // the fastest shape; among shapes within 1.5% of it (timing noise), the one with the fewest
-    // source splits (fewer FP64 slices written and re-read), then the fewest work items
-    for (const Cand &c : timed) best = std::min(best, c.ms);
+    // source splits (fewer FP64 slices written and re-read), then the fewest work items; none that is
+    // slower than the plan's own (the longest time of the listed shapes that make the same launch)
+    const Cand mine = timed[own_at];
+    double own_ms = mine.ms;
+    for (const Cand &c : timed) {
+        best = std::min(best, c.ms);
+        if (c.sh.tpl == own.tpl && c.sh.per == own.per && c.n_split == mine.n_split && c.n_items == mine.n_items)
+            own_ms = std::max(own_ms, c.ms);
+    }
     const Cand *pick = nullptr;
     for (const Cand &c : timed)
-        if (c.ms <= 1.015 * best &&
-            (!pick || c.n_split < pick->n_split || (c.n_split == pick->n_split && c.mi < pick->mi)))
+        if (c.ms <= std::min(1.015 * best, own_ms) &&
+            (!pick || c.n_split < pick->n_split || (c.n_split == pick->n_split && c.sh.mi < pick->sh.mi)))
             pick = &c;
     if (pick) {
-        btpl = pick->tpl;
-        bmi = pick->mi;
-        bper = pick->per != 0;
+        btpl = pick->sh.tpl;
+        bmi = pick->sh.mi;
+        bper = pick->sh.per != 0;
         best = pick->ms;
     }
     p->tuned_tpl = btpl;
