@@ -34,19 +34,27 @@ __device__ __forceinline__ void rsq_cluster_end() {
     __builtin_amdgcn_s_setprio(0);
 }
 
-// p[0] + p[stride] + ... (n values) in order, their loads issued eight at a time: a loop of n dependent
-// loads and adds took 14 us of a launch for 14 split slices, 5 us so.
+// The next U of p's values, m of them there (1 <= m <= U; the last one is read again), added to s in order
+template <int U, class T>
+__device__ __forceinline__ void add_group(T &s, const T *__restrict__ p, int64_t stride, int m) {
+    T v[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) v[q] = p[min(q, m - 1) * stride];
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+        if (q < m) s += v[q];
+}
+
+// p[0] + p[stride] + ... (n values) in order, their loads issued up to eight at a time: a loop of n
+// dependent loads and adds took 14 us of a launch for 14 split slices, 5 us so.  The last group is of the
+// size that holds what is left: with eight loads whatever was left, the projection of one
+// FP64 body took 4.7 us (a plain loop 4.1, so 4.0).
 template <class T>
 __device__ __forceinline__ T strided_sum(const T *__restrict__ p, int64_t stride, int n) {
     T s = T(0);
-    for (int k = 0; k < n; k += 8) {
-        T v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = p[min(k + q, n - 1) * stride];
-#pragma unroll
-        for (int q = 0; q < 8; ++q)
-            if (k + q < n) s += v[q];
-    }
+    for (; n > 4; n -= 8, p += 8 * stride) add_group<8>(s, p, stride, min(n, 8));
+    if (n > 2) add_group<4>(s, p, stride, n);
+    else if (n > 0) add_group<2>(s, p, stride, n);
     return s;
 }
 
