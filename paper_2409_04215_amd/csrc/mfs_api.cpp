@@ -138,16 +138,48 @@ int generate_p2p_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
                 const double nsrc = (double)(body_src_ptr[c1] - body_src_ptr[c0]);
                 items[n] = it;
                 work[n] = nsrc * (double)(t1 - t0) * (kind == MFS_STOKES ? 2.5 : 1.0);
-                order[n] = (int32_t)n;
                 ++n;
             }
         }
     }
-    // largest work first (ties in generation order), so the dispatcher schedules greedily
-    std::sort(order, order + n, [&](int32_t a, int32_t b) { return work[a] > work[b] || (work[a] == work[b] && a < b); });
-    for (int64_t i = 0; i < n; ++i) sorted[i] = items[order[i]];
     *n_items = n;
     *n_split_out = n_split;
+    // largest work first (ties in generation order), so the dispatcher schedules greedily.  Most launches
+    // have a handful of amounts of work (whole and cut blocks and chunks of each system), so the items are
+    // counted by amount: 45000 items of 300 bodies 0.4 ms, 2.3 ms sorted
+    constexpr int kAmounts = 256;
+    double amount[kAmounts];
+    int64_t at[kAmounts] = {};
+    int n_amount = 0;
+    bool few = true;
+    for (int64_t i = 0; i < n && few; ++i) {
+        int k = i > 0 && work[i] == work[i - 1] ? order[i - 1] : n_amount - 1;
+        while (k >= 0 && amount[k] != work[i]) --k;
+        if (k < 0) {
+            few = n_amount < kAmounts;
+            if (!few) break;
+            k = n_amount++;
+            amount[k] = work[i];
+        }
+        order[i] = k;
+        ++at[k];
+    }
+    if (few) {
+        int rank[kAmounts];
+        std::iota(rank, rank + n_amount, 0);
+        std::sort(rank, rank + n_amount, [&](int a, int b) { return amount[a] > amount[b]; });
+        int64_t next = 0;
+        for (int r = 0; r < n_amount; ++r) {
+            const int64_t count = at[rank[r]];
+            at[rank[r]] = next;
+            next += count;
+        }
+        for (int64_t i = 0; i < n; ++i) sorted[at[order[i]]++] = items[i];
+        return MFS_OK;
+    }
+    std::iota(order, order + n, 0);
+    std::sort(order, order + n, [&](int32_t a, int32_t b) { return work[a] > work[b] || (work[a] == work[b] && a < b); });
+    for (int64_t i = 0; i < n; ++i) sorted[i] = items[order[i]];
     return MFS_OK;
 }
 
@@ -248,6 +280,21 @@ int build_p2p_items(P2PPlan &pp, int64_t n_sys, const int64_t *sys_body_ptr, con
     if (!pp.items.empty()) MFS_TRY(upload_vec(pp.d_items, pp.items, s));
     MFS_TRY(pp.d_counter.reserve(sizeof(int)));
     return MFS_OK;
+}
+
+// The same items once more (one workgroup per item), without making them again.
+static int copy_p2p_items(P2PPlan &to, const P2PPlan &from, hipStream_t s) {
+    to.items = from.items;
+    to.n_split = from.n_split;
+    to.tpl = from.tpl;
+    to.far = from.far;
+    to.wide = from.wide;
+    const size_t bytes = from.items.size() * sizeof(P2PItem);
+    if (bytes) {
+        MFS_TRY(to.d_items.reserve(bytes));
+        MFS_HIP_TRY(hipMemcpyAsync(to.d_items.ptr, from.d_items.ptr, bytes, hipMemcpyDeviceToDevice, s));
+    }
+    return to.d_counter.reserve(sizeof(int));
 }
 
 }  // namespace mfs
@@ -1536,10 +1583,8 @@ int mfs_plan_create(mfs_plan *out, const mfs_plan_desc *d, void *stream) {
                                 p->gam_off.data(), p->kind.data(), p->mu, 1, min_items, s));
         MFS_TRY(build_p2p_items(p->p2p_tr, p->n_sys, p->sys_body_ptr.data(), src_row.data(), trg_row.data(),
                                 p->lam_off.data(), p->kind.data(), p->mu, 1, min_items, s));
-        MFS_TRY(build_p2p_items(p->p2p_fwd1, p->n_sys, p->sys_body_ptr.data(), trg_row.data(), src_row.data(),
-                                p->gam_off.data(), p->kind.data(), p->mu, 1, min_items, s));
-        MFS_TRY(build_p2p_items(p->p2p_tr1, p->n_sys, p->sys_body_ptr.data(), src_row.data(), trg_row.data(),
-                                p->lam_off.data(), p->kind.data(), p->mu, 1, min_items, s));
+        MFS_TRY(copy_p2p_items(p->p2p_fwd1, p->p2p_fwd, s));
+        MFS_TRY(copy_p2p_items(p->p2p_tr1, p->p2p_tr, s));
         MFS_TRY(build_far_items(p.get(), min_items, false, s));
     }
     // workspace
