@@ -95,8 +95,10 @@ const char *mfs_version(void);
  * host thread and device (allocated on first use; growing it waits for the
  * device).  The first call with a given structure (the three pointer arrays,
  * mu and the entry point) also builds the work tables of its launch and keeps
- * them for later calls with the same structure (up to 8 structures per
- * workspace; evicting one waits for the device).  Calls of one host thread on
+ * them for later calls with the same structure; mixed pair sums have tables of
+ * their own, which calls whose output shares memory with an input do not use
+ * (up to 16 sets of tables per workspace, so 8 structures in both precisions;
+ * evicting one waits for the device).  Calls of one host thread on
  * different streams share that workspace and must not overlap.
  * Errors: MFS_EINVAL for NULL data pointers, n_sys < 1, bad structure arrays,
  * unknown flags or precision.

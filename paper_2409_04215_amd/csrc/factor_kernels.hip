@@ -260,7 +260,7 @@ __global__ __launch_bounds__(FB) void wy_apply_kernel(const double *__restrict__
 //    meanwhile (52 to 67 us a step);
 //  * Q and R^-1 are one launch each, 16 columns per workgroup in registers.
 // 2400 x 1200 (QR, Q and R^-1): 32.0 ms before, 6.4 ms now (4.4, 1.55 and 0.37), plan
-// creation 34.7 -> 9.2 ms.  sqrt and the divisions are not what a column step waits
+// creation 34.6 -> 7.7 ms.  sqrt and the divisions are not what a column step waits
 // for: through v_rsq_f64 and v_rcp_f64 a panel took the same 40 us.
 // ---------------------------------------------------------------------------
 constexpr int QT = 512;        // threads

@@ -192,7 +192,8 @@ int generate_p2p_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
 // (18 ms) 18700 / 18760 / 17830 / 17220 / 17020.  T from 2.8e12 Stokes or twice as many
 // Laplace pairs per second, and of the largest system alone: the items of a batch differ in
 // size and are handed out largest first, so the small systems fill the last round (12 systems
-// of 17 to 62 bodies: 529 us at 5500 items, 565 at 10000).
+// of 17 to 62 bodies: 529 us at 5500 items, 565 at 10000).  FP64 sums, at under half these rates,
+// take the same items: 4 to 160 bodies of 331 x 667 are 0.5 to 30% faster than with 16384.
 int default_min_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                       const int64_t *body_src_ptr, const int32_t *kind_of_body, int kind_all, int most) {
     double us = 0.0;
@@ -208,11 +209,11 @@ int default_min_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t 
 
 // Whether the sums of this orientation use far tiles: Laplace bodies only (beside them the Stokes
 // items of a launch would run with the far walk's registers, 4 waves per SIMD: 585 us instead of
-// 532 for a batch of both), a system of at least
-// 32 bodies (below, most are near some of an item's targets) and 2.5e8 pairs (below, 256 targets
-// to an item leave the chip too few: 48 bodies of 200 x 400 took 66 us instead of 60, 32 of
-// 389 x 777 79 us instead of 86), whole tiles but for a quarter, and bodies of at most 1024 sources (their
-// strengths stay in LDS, 4 KB a wave).
+// 532 for a batch of both), a system of at least 32 bodies (below, most are near some of an item's
+// targets: 28 of 389 x 777 take 52.2 us with far tiles, 53.7 without, 36 73.9 and 82.5) and 2.5e8 pairs
+// (below, 256 targets to an item leave the chip too few: 48 bodies of 200 x 400, 1.8e8 pairs, 48.0 us
+// and 45.7; 56, 2.5e8, 58.1 and 59.3; 120 of 100 x 200, 2.9e8, 70.0 and 70.2), whole tiles but for a
+// quarter, and bodies of at most 1024 sources (their strengths stay in LDS, 4 KB a wave).
 bool use_far_tiles(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                    const int64_t *body_src_ptr, const int32_t *kind_of_body, std::vector<int32_t> &tile_ptr) {
     int64_t most = 0, sources = 0, tiles = 0;
@@ -241,8 +242,8 @@ bool use_far_tiles(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *bo
 // source of their system, one launch): when that many workgroups fit the chip at once and the longest
 // of them, S sources on one CU (its waves share the LDS that they read the sources from: 7.7 ns a
 // Stokes source, 3.5 Laplace), takes no more than the sum on all CUs plus the launches saved.  Both
-// sides, us: Stokes 4 bodies of 300 x 600 25.7 general, 19.1 wide; 6 of 400 x 800 24.2, 24.8; 10 of
-// 300 x 600 24.7, 29.3; Laplace 20 of 400 x 800 39.6, 32.9; 6 of 200 x 400 in 6 systems 24.6, 21.3.
+// sides, us: Stokes 4 bodies of 300 x 600 19.1 general, 13.7 wide; 6 of 400 x 800 18.3, 20.9; 10 of
+// 300 x 600 18.4, 25.7; Laplace 20 of 400 x 800 35.2, 31.5; 6 of 200 x 400 in 6 systems 18.1, 13.3.
 bool use_wide_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                     const int64_t *body_src_ptr, int kind) {
     constexpr double saved_us = 11.0;

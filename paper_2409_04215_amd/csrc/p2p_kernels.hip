@@ -186,7 +186,7 @@ struct KernelArgs {
 // own in the block and extreme scales take the VALU path.
 // Rate: a pair is v_rsq_f32 and one FMA on the VALU (5.2 ns per 64 pairs and SIMD in a bare
 // loop, 13.3 with the six operations of r^2), the MFMA (1.7 ns) runs beside them.
-// 250 bodies, 389 sources and 777 targets each: 3285 -> 2387 us (7.9e12 pairs/s).
+// 250 bodies, 389 sources and 777 targets each: 3285 -> 2430 us (7.7e12 pairs/s).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float bf16_head(float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); }
 __device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {  // both exact in bf16
@@ -532,7 +532,7 @@ __device__ __forceinline__ void laplace_far_item(const KernelArgs &a, const P2PI
 // sources of their system, wave w the w-th sixteenth, so there is nothing left to add up, and makes
 // the operands from the caller's points: the sources of a run on their way to LDS, the target's
 // offset from a body's first source directly (one rounding where the two offsets of
-// operands_kernel have two).  4 Stokes bodies, 300 sources and 600 targets each: 25.7 -> 19.1 us.
+// operands_kernel have two).  4 Stokes bodies, 300 sources and 600 targets each: 19.1 -> 13.7 us.
 // ---------------------------------------------------------------------------
 struct RawPoints {
     const double *trg, *src, *str;  // [n][3], [n][3], [n][3] or [n]
