@@ -183,17 +183,20 @@ int generate_p2p_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
     return MFS_OK;
 }
 
-// The least number of work items of a pair-sum launch of this size.  A launch holds about 2048
-// workgroups at a time, so with n items the last round idles about 2048 / 2n of the chip's
+// The least number of work items of a pair-sum launch that takes us microseconds.  A launch holds
+// about 2048 workgroups at a time, so with n items the last round idles about 2048 / 2n of the chip's
 // time T, and an item costs about 8 us of a workgroup's beside its pairs (set-up, the sum over
 // its waves, its part of the slice sums); the sum of both is least at n = 2048 sqrt(T / 16 us).
 // Measured (matvec, us, at 2048 / 4096 / 8192 / 16384 / 32768 items): 50 bodies (T = 0.16 ms)
 // 206 / 197 / 203 / 214 / 212, 80 bodies (0.4 ms) 471 / 452 / 443 / 449 / 481, 400 bodies
-// (18 ms) 18700 / 18760 / 17830 / 17220 / 17020.  T from 2.8e12 Stokes or twice as many
-// Laplace pairs per second, and of the largest system alone: the items of a batch differ in
-// size and are handed out largest first, so the small systems fill the last round (12 systems
-// of 17 to 62 bodies: 529 us at 5500 items, 565 at 10000).  FP64 sums, at under half these rates,
-// take the same items: 4 to 160 bodies of 331 x 667 are 0.5 to 30% faster than with 16384.
+// (18 ms) 18700 / 18760 / 17830 / 17220 / 17020.
+int min_items_for(double us, int most) {
+    return (int)std::min((double)most, std::max(2048.0, 2048.0 * std::sqrt(us / 16.0)));
+}
+
+// Plans: T from 2.8e12 Stokes or twice as many Laplace pairs per second, and of the largest system
+// alone: the items of a batch differ in size and are handed out largest first, so the small systems
+// fill the last round (12 systems of 17 to 62 bodies: 529 us at 5500 items, 565 at 10000).
 int default_min_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
                       const int64_t *body_src_ptr, const int32_t *kind_of_body, int kind_all, int most) {
     double us = 0.0;
@@ -204,7 +207,31 @@ int default_min_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t 
         us = std::max(us, (double)(body_trg_ptr[b1] - body_trg_ptr[b0]) * (double)(body_src_ptr[b1] - body_src_ptr[b0]) /
                               (kind == MFS_STOKES ? 2.8e6 : 5.6e6));
     }
-    return (int)std::min((double)most, std::max(2048.0, 2048.0 * std::sqrt(us / 16.0)));
+    return min_items_for(us, most);
+}
+
+// Standalone calls: the same for one system (also in FP64, where twice as many items are up to 3%
+// slower: 60 bodies of 331 x 667 607 us, 622).  A batch takes T of all its systems, with the rates of
+// FP64 sums (1.3e12 and 2.3e12) unless it is a mixed sum (fields and gradients share their tables
+// between the precisions), and half the T for mixed sums.  With T of the largest system batches took
+// too few, us: 11 Stokes systems of 25 to 94 bodies of 160 x 367 1045, now 974, in FP64 2246 and 1968;
+// 12 of 8 to 31 bodies of 300 x 600 in FP64 854 and 777; and with the whole T of mixed sums too many:
+// 8 Laplace systems of 12 to 45 bodies of 400 x 800 317, now 297.  Launches with far tiles keep the
+// plans' rule: their items are few and long, and cutting one large system in a batch gives every small
+// one as many empty items (32 bodies beside 500 systems of two: 187 us, 326 with this rule).
+int standalone_min_items(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t *body_trg_ptr,
+                         const int64_t *body_src_ptr, int kind, bool mixed, bool far, int most) {
+    double pairs = 0.0;
+    int systems = 0;
+    for (int64_t sy = 0; sy < n_sys; ++sy) {
+        const int64_t b0 = sys_body_ptr[sy], b1 = sys_body_ptr[sy + 1];
+        pairs += (double)(body_trg_ptr[b1] - body_trg_ptr[b0]) * (double)(body_src_ptr[b1] - body_src_ptr[b0]);
+        systems += b1 > b0;
+    }
+    if (far || systems <= 1)
+        return default_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, kind, most);
+    const bool stokes = kind == MFS_STOKES;
+    return min_items_for(mixed ? pairs / (stokes ? 5.6e6 : 11.2e6) : pairs / (stokes ? 1.3e6 : 2.3e6), most);
 }
 
 // Whether the sums of this orientation use far tiles: Laplace bodies only (beside them the Stokes
@@ -323,7 +350,7 @@ struct Layout {
     uint64_t last_use = 0;
 };
 
-// launch shape of the standalone pair sums: one target per lane, default_min_items up to this
+// launch shape of the standalone pair sums: one target per lane, standalone_min_items up to this
 // many (the allocation-free call holds the items and slices of that many)
 constexpr int kStandaloneMinItems = 16384;
 // and of the plans' pair sums until they are tuned or set
@@ -429,8 +456,6 @@ int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_s
     std::vector<int64_t> out_ptr(nb + 1);
     for (int64_t b = 0; b <= nb; ++b) out_ptr[b] = dim * body_trg_ptr[b];
     std::vector<int32_t> kob(std::max<int64_t>(1, nb), kind);
-    const int min_items = default_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, kind,
-                                            kStandaloneMinItems);
     // One walk or the other: their items differ (64 and 256 targets).  Where both rules hold, the two take the
     // same time (us, wide and far: 32 bodies of 500 x 512 58 and 56, 199 of 84 x 82 72 and 73, 2 x 40 of
     // 400 x 204 55 and 59; without either 72, 114, 75), so the one that needs no operands is taken.
@@ -443,8 +468,11 @@ int layout(Workspace &ws, int variant, int kind, int dim, double mu, int64_t n_s
         l->n_tiles = l->tiles_h.back();
         MFS_TRY(upload_vec(l->tile_ptr, l->tiles_h, s));
     }
+    const int min_items = wide ? 1
+                               : standalone_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, kind, mixed,
+                                                      l->far, kStandaloneMinItems);
     MFS_TRY(build_p2p_items(l->pp, n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, out_ptr.data(), kob.data(), mu, 1,
-                            wide ? 1 : min_items, s, l->far));
+                            min_items, s, l->far));
     l->pp.wide = wide;
     l->last_use = ++ws.clock;
     *out = l.get();
@@ -1267,13 +1295,14 @@ int p2p_stokes_noalloc(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
         return fail(MFS_EINVAL, "mfs_p2p_stokes_noalloc takes at most " + std::to_string(kNoAllocMaxBodies) + " bodies");
     if (nt == 0) return MFS_OK;
     hipStream_t s = (hipStream_t)stream;
+    const bool overlap = overlaps_inputs(out, 3 * nt, trg_xyz, src_xyz, str, nt, ns, 3);
     std::lock_guard<std::mutex> lock(g_noalloc_mutex);
     NoAllocHost &h = g_noalloc_host;
     int64_t n_items = 0;
     int n_split = 1;
     MFS_TRY(generate_p2p_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, 3, nullptr, MFS_STOKES, mu, 1,
-                               default_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, MFS_STOKES,
-                                                 kStandaloneMinItems),
+                               standalone_min_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, MFS_STOKES,
+                                                    prec == MFS_MIXED && !overlap, false, kStandaloneMinItems),
                                h.items, h.work, h.order, h.sorted, kNoAllocMaxItems, &n_items,
                                &n_split));
     // scratch layout (256-byte aligned pieces)
@@ -1290,8 +1319,7 @@ int p2p_stokes_noalloc(int64_t n_sys, const int64_t *sys_body_ptr, const int64_t
         return fail(MFS_EINVAL, "mfs_p2p_stokes_noalloc needs " + std::to_string(need) +
                                     " bytes of scratch for these sizes; it holds " + std::to_string(kScratchBytes));
     // checked above on the general items, so that what is refused does not depend on the walk
-    const bool wide = f32 && use_wide_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, MFS_STOKES) &&
-                      !overlaps_inputs(out, 3 * nt, trg_xyz, src_xyz, str, nt, ns, 3);
+    const bool wide = f32 && use_wide_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, MFS_STOKES) && !overlap;
     if (wide)
         MFS_TRY(generate_p2p_items(n_sys, sys_body_ptr, body_trg_ptr, body_src_ptr, nullptr, 3, nullptr, MFS_STOKES, mu,
                                    1, 1, h.items, h.work, h.order, h.sorted, kNoAllocMaxItems, &n_items, &n_split));
