@@ -129,14 +129,14 @@ def _ptr(t: Optional[torch.Tensor]):
 def _result(flags, sys_ptr, ptr, *shape, device):
     """A new output for the points of a standalone call: the library writes those of the bodies that
     the systems use, the first sys_ptr[-1], or adds to zeros with ACCUMULATE; other points stay zero."""
-    used = sys_ptr[-1] if len(sys_ptr) else -1
-    whole = 0 <= used < len(ptr) and shape[0] == ptr[used]
+    used = sys_ptr.item(-1) if sys_ptr.size else -1
+    whole = 0 <= used < ptr.size and ptr.item(used) == shape[0]
     new = torch.empty if whole and not flags & ACCUMULATE else torch.zeros
     return new(*shape, dtype=torch.float64, device=device)
 
 
 def _host_i64(a) -> np.ndarray:
-    return np.ascontiguousarray(np.asarray(a, dtype=np.int64))
+    return np.ascontiguousarray(a, dtype=np.int64)
 
 
 def _ip64(a: np.ndarray):
